@@ -180,12 +180,7 @@ __device__ __forceinline__ void pin3(float* x) {
 
 // Per-lane constants copied once into registers.
 template <int MAXDOF>
-__device__ __forceinline__ void pin_consts(BodyT& B, JointT& J, bool has_joint, ContactT* C, int nc) {
-  pin(B.inv_m);
-  pin3(B.I);
-  pin3(B.Iinv);
-  pin3(B.free_p);
-  pin3(B.free_r);
+__device__ __forceinline__ void pin_joint(JointT& J, bool has_joint) {
   if (has_joint) {
     pin3(J.ap);
     pin3(J.ac);
@@ -204,6 +199,15 @@ __device__ __forceinline__ void pin_consts(BodyT& B, JointT& J, bool has_joint, 
       pin(J.gear[k]);
     }
   }
+}
+template <int MAXDOF>
+__device__ __forceinline__ void pin_consts(BodyT& B, JointT& J, bool has_joint, ContactT* C, int nc) {
+  pin(B.inv_m);
+  pin3(B.I);
+  pin3(B.Iinv);
+  pin3(B.free_p);
+  pin3(B.free_r);
+  pin_joint<MAXDOF>(J, has_joint);
   for (int c = 0; c < nc; ++c) {
     pin3(C[c].l);
     pin(C[c].rho);
@@ -255,6 +259,13 @@ __device__ __forceinline__ void xch_get2(const XchRows* X, int src, v3& a, v3& b
   const float2 x1 = *reinterpret_cast<const float2*>(&X->r[src][1]);
   a = V(x0.x, x0.y, x0.z);
   b = V(x0.w, x1.x, x1.y);
+}
+// Barrier of a block whose wavefronts exchange LDS rows: every LDS access
+// issued before it is complete, and none after it is moved up.
+__device__ __forceinline__ void block_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 // A full body state or its cotangent (p, q, v, w: columns 0-12).
 template <class S>

@@ -93,6 +93,7 @@ struct brax_sys {
   int32_t* d_env_list = nullptr;
   int32_t* d_type_off = nullptr;
   size_t lds_limit = LDS_LIMIT_GFX950;  // per-workgroup LDS of the device
+  int n_cu = 256;                       // its compute units
   // fused schedule
   int envs_per_wave[MAXT] = {0};
   int waves_per_block = 1;
@@ -123,6 +124,7 @@ struct brax_sys {
     c.Bm = Bm;
     c.Am = Am;
     c.n_types = n_types;
+    c.n_cu = n_cu;
     c.env_type = d_env_type;
     c.env_list = d_env_list;
     c.type_off = d_type_off;
@@ -325,6 +327,9 @@ int brax_sys_create(const char* const* descs, int32_t n_descs, const int32_t* en
     int lds = 0;
     HIP_TRY(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device));
     if (lds > 0) s->lds_limit = (size_t)lds;
+    int n_cu = 0;
+    HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device));
+    if (n_cu > 0) s->n_cu = n_cu;
   }
   auto dmalloc = [&](void** p, size_t n) -> int {
     if (n == 0) n = 4;
@@ -674,10 +679,7 @@ static int autotune_impl(brax_sys* s, const brax_state* in, const float* act, in
                        st) != hipSuccess)
         rc = fail(BRAX_E_DEVICE, "autotune reset failed");
   }
-  int n_cu = 0;
-  if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, s->device) != hipSuccess || n_cu <= 0)
-    n_cu = 256;
-  const int n_simd = 4 * n_cu;  // four SIMDs per compute unit
+  const int n_simd = 4 * s->n_cu;  // four SIMDs per compute unit
   // candidates: environments per wavefront (per type) and wavefronts per block
   const int wpb_c[] = {1, 2, 4};
   int best_epw[MAXT];

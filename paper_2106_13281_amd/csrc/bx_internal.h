@@ -88,6 +88,7 @@ struct LaunchCtx {
   const Tables* host_tab;       // host copy (sizes, counts)
   int E, Bm, Am;
   int n_types;
+  int n_cu;                     // compute units of the device
   const int32_t* env_type;      // device [E]
   const int32_t* env_list;      // device, grouped by type
   const int32_t* type_off;      // device [n_types]

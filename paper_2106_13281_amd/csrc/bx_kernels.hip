@@ -7,6 +7,8 @@
 // (the global environment ids of type t are env_list[off_t .. off_t + n_t)).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "bx_access.h"
 #include "bx_internal.h"
 #include "bx_pair_lanes.h"
@@ -319,6 +321,140 @@ __device__ __forceinline__ PairLanes* pair_lanes(float4* lds) {
   return reinterpret_cast<PairLanes*>(reinterpret_cast<XchRows*>(lds) + (blockDim.x >> 6)) + (threadIdx.x >> 6);
 }
 
+// A lane's ground-contact candidates: the first REGC from registers (no
+// dynamic indexing; a slot no body of the type has is skipped by the whole
+// wave), the rest from the table C. Adds the velocity changes to dv, dw and
+// the applied candidates to cnt.
+// PEN_FIRST (two in registers): the penetrating candidates first, in
+// candidate order (the same sums), so that the second evaluation's impulse
+// runs only where a lane has two penetrating candidates, not wherever one has
+// its second (measured per kernel: biped 14.0 -> 13.0 ms, planar runner 10.3
+// -> 10.0, grasp 24.7 -> 24.2; the contact-lane kernels without body-body
+// contacts lost 2-3% and keep the plain order).
+template <int REGC, bool PEN_FIRST>
+__device__ __forceinline__ void ground_contacts(const ContactT* __restrict__ C, const ContactT (&Creg)[REGC], int n_con,
+                                                int max_con, const TypeT& ty, const BodyT& B, const Body& s,
+                                                const Frame& f, v3& dv, v3& dw, int& cnt) {
+  if (PEN_FIRST) {
+    const v3 rl0 = mul(f.R, ld3(Creg[0].l)), rl1 = mul(f.R, ld3(Creg[REGC - 1].l));
+    const float d0 = Creg[0].rho - (s.p.z + rl0.z), d1 = Creg[REGC - 1].rho - (s.p.z + rl1.z);
+    const bool p0 = 0 < max_con && n_con > 0 && d0 > 0.f;
+    const bool p1 = 1 < max_con && n_con > 1 && d1 > 0.f;
+    if (p0 || p1)
+      cnt += contact_apply(p0 ? Creg[0].rho : Creg[REGC - 1].rho, ty, B, s, f, sel(p0, rl0, rl1), p0 ? d0 : d1, dv, dw)
+                 ? 1
+                 : 0;
+    if (p0 && p1) cnt += contact_apply(Creg[REGC - 1].rho, ty, B, s, f, rl1, d1, dv, dw) ? 1 : 0;
+  } else {
+#pragma unroll
+    for (int k = 0; k < REGC; ++k)
+      if (k < max_con && n_con > k) cnt += contact_eval(Creg[k], ty, B, s, f, dv, dw) ? 1 : 0;
+  }
+  for (int c = REGC; c < n_con; ++c) cnt += contact_eval(C[c], ty, B, s, f, dv, dw) ? 1 : 0;
+}
+
+// A body's contact candidates spread over its lane group: every lane of the
+// group adds the group's sums in group order (the same total on each, so the
+// copies of the state stay equal), through the exchange rows X.
+__device__ __forceinline__ void lane_group_sums(XchRows* X, int lane, int base, int b, const TypeT& ty, const BodyT& B,
+                                                v3& dv, v3& dw, int& cnt) {
+  X->r[lane][0] = make_float4(dv.x, dv.y, dv.z, (float)cnt);
+  X->r[lane][1] = make_float4(dw.x, dw.y, dw.z, 0.f);
+  v3 sv = V(0.f, 0.f, 0.f), sw = sv;
+  int sc = 0;
+  // four rows read together, then added in order (a group has at most 8 lanes)
+  for (int i0 = 0; i0 < ty.max_ng; i0 += 4) {
+    float4 gv[4], gw[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = i0 + j;
+      const int src = base + (i < B.ng ? (int)((B.grp_packed >> (4 * (i & 7))) & 15u) : b);
+      gv[j] = X->r[src][0];
+      gw[j] = X->r[src][1];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (i0 + j < B.ng) {
+        sv += V(gv[j].x, gv[j].y, gv[j].z);
+        sw += V(gw[j].x, gw[j].y, gw[j].z);
+        sc += (int)gv[j].w;
+      }
+    }
+  }
+  dv = sv;
+  dw = sw;
+  cnt = sc;
+}
+
+// The environment layer on the stepped state s of one environment's lanes
+// (see EnvArgs): reward and termination, the reset of a finished environment
+// (its state replaces s) and the observation. Returns whether this lane's
+// environment has finished.
+template <int MAXDOF>
+__device__ __forceinline__ bool env_epilogue(const EnvArgs& ea, int t, const TypeT& ty, const JointT& J, bool has_joint,
+                                             int src_parent, const float* raw, float x_before, bool live, int b, int bs,
+                                             int base, int e, int Bm, int E, Body& s) {
+  const int nb = ty.nb;
+  // reward and termination from the stepped state (the root's lane holds it)
+  const EnvT P = ea.env[t];
+  const int rl = base + P.root;
+  const float x0 = shfl(x_before, rl), x1 = shfl(s.p.x, rl), z1 = shfl(s.p.z, rl);
+  const bool healthy = z1 >= P.z_min && z1 <= P.z_max;
+  const bool finished = !healthy;
+  // control cost: the squared actions as passed, summed over the
+  // environment's lanes in body order
+  float sq = 0.f;
+  for (int x = 0; x < MAXDOF; ++x) sq += raw[x] * raw[x];
+  float ctrl = 0.f;
+  for (int i = 0; i < nb; ++i) ctrl += shfl(sq, base + i);
+  if (live && b == P.root) {
+    ea.reward[e] = P.forward_weight * (x1 - x0) / ty.dt + (healthy ? P.healthy_reward : 0.f) - P.ctrl_cost * ctrl;
+    ea.done[e] = healthy ? 0 : 1;
+  }
+  // a finished environment continues from its reset state
+  if (finished && live) s = load_body(ea.reset, bs, e, Bm, E);
+  // observation of the final state: joint angles and relative angular
+  // velocity about each Euler axis on the child's lane (the parent's
+  // rotation and angular velocity read across lanes), the root's entries
+  // and the padding on the root's lane
+  const m3 Rf = quat_to_mat(s.q);
+  m3 RPf;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) RPf.m[i] = shfl(Rf.m[i], src_parent);
+  const v3 wP = V(shfl(s.w.x, src_parent), shfl(s.w.y, src_parent), shfl(s.w.z, src_parent));
+  const JointGeo g = joint_geo<MAXDOF>(J, RPf, joint_child<MAXDOF>(J, s, Rf));
+  const v3 wrel = s.w - wP;
+  const int D = ty.ndof;
+  if (live && has_joint && b < nb) {
+    for (int k = 0; k < MAXDOF; ++k) {
+      if (k < J.dof) {
+        ea.obs[(size_t)(11 + J.dof0 + k) * E + e] = g.th[k];
+        ea.obs[(size_t)(11 + D + J.dof0 + k) * E + e] = dot(wrel, g.ax[k]);
+      }
+    }
+  }
+  if (live && b == P.root) {
+    const float head[11] = {s.p.z, s.q.w, s.q.x, s.q.y, s.q.z, s.v.x, s.v.y, s.v.z, s.w.x, s.w.y, s.w.z};
+#pragma unroll
+    for (int k = 0; k < 11; ++k) ea.obs[(size_t)k * E + e] = head[k];
+    for (int k = 11 + 2 * D; k < ea.Omax; ++k) ea.obs[(size_t)k * E + e] = 0.f;
+  }
+  return finished;
+}
+
+// The final state of body lane b; the padded body slots of a smaller system
+// are written as zeros (a finished environment's as its reset state's).
+__device__ __forceinline__ void store_result(const Fields& out, const Body& s, int nb, int b, int e, int Bm, int E,
+                                             bool finished, const Fields& reset) {
+  store_body(out, 0, s, b, e, Bm, E);
+  for (int pb = nb + b; pb < Bm; pb += nb) {
+    if (finished)
+      store_body(out, 0, load_body(reset, pb, e, Bm, E), pb, e, Bm, E);
+    else
+      zero_body(out, pb, e, Bm, E);
+  }
+}
+
 // TAPE: also write each substep's tape record (state before the kinematic
 // update, total torque, count of applied contacts) to the wavefront-major
 // tape[step][sub][work item w of n_work][TAPE_N][64], for the adjoint that
@@ -409,34 +545,11 @@ __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const 
       Frame f = derive_inv(B, R);
       JointChild jc = joint_child<MAXDOF>(J, s, R);
       // the contact candidates while the parent's state is in flight (they
-      // need none of it): the first REGC from registers (no dynamic indexing;
-      // a slot no body of the type has is skipped by the whole wave), the
-      // rest from the table
+      // need none of it)
       v3 dv = V(0.f, 0.f, 0.f), dw = V(0.f, 0.f, 0.f);
       int cnt = 0;
-      if (REGC == 2 && !TAPE && (!CL || PAIRS)) {
-        // the penetrating candidates first, in candidate order (the same
-        // sums), so that the second evaluation's impulse runs only where a
-        // lane has two penetrating candidates, not wherever one has its
-        // second (measured per kernel: biped 14.0 -> 13.0 ms, planar runner
-        // 10.3 -> 10.0, grasp 24.7 -> 24.2; the contact-lane kernels without
-        // body-body contacts lost 2-3% and keep the plain order)
-        const v3 rl0 = mul(f.R, ld3(Creg[0].l)), rl1 = mul(f.R, ld3(Creg[REGC - 1].l));
-        const float d0 = Creg[0].rho - (s.p.z + rl0.z), d1 = Creg[REGC - 1].rho - (s.p.z + rl1.z);
-        const bool p0 = 0 < max_con && n_con > 0 && d0 > 0.f;
-        const bool p1 = 1 < max_con && n_con > 1 && d1 > 0.f;
-        if (p0 || p1)
-          cnt += contact_apply(p0 ? Creg[0].rho : Creg[REGC - 1].rho, ty, B, s, f, sel(p0, rl0, rl1), p0 ? d0 : d1,
-                               dv, dw)
-                     ? 1
-                     : 0;
-        if (p0 && p1) cnt += contact_apply(Creg[REGC - 1].rho, ty, B, s, f, rl1, d1, dv, dw) ? 1 : 0;
-      } else {
-#pragma unroll
-        for (int k = 0; k < REGC; ++k)
-          if (k < max_con && n_con > k) cnt += contact_eval(Creg[k], ty, B, s, f, dv, dw) ? 1 : 0;
-      }
-      for (int c = REGC; c < n_con; ++c) cnt += contact_eval(tab->contact[t][cfirst + c], ty, B, s, f, dv, dw) ? 1 : 0;
+      ground_contacts<REGC, REGC == 2 && !TAPE && (!CL || PAIRS)>(&tab->contact[t][cfirst], Creg, n_con, max_con, ty, B, s,
+                                                                  f, dv, dw, cnt);
       // joint evaluated on every lane (a root uses its own state as the
       // parent and its result is discarded)
       JointOut jo = joint_eval<MAXDOF>(J, P, RP, s, jc, a);
@@ -469,38 +582,8 @@ __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const 
           torque -= tq;
         }
       }
-      // a body's contact candidates spread over its lane group: every lane of
-      // the group adds the group's sums in group order (the same total on
-      // each, so the copies of the state stay equal); the exchange rows are
-      // free once the children's reactions have been read
-      if (LANES && nl > nb) {
-        X->r[lane][0] = make_float4(dv.x, dv.y, dv.z, (float)cnt);
-        X->r[lane][1] = make_float4(dw.x, dw.y, dw.z, 0.f);
-        v3 sv = V(0.f, 0.f, 0.f), sw = sv;
-        int sc = 0;
-        // four rows read together, then added in order (a group has at most 8 lanes)
-        for (int i0 = 0; i0 < ty.max_ng; i0 += 4) {
-          float4 gv[4], gw[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int i = i0 + j;
-            const int src = base + (i < B.ng ? (int)((B.grp_packed >> (4 * (i & 7))) & 15u) : b);
-            gv[j] = X->r[src][0];
-            gw[j] = X->r[src][1];
-          }
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (i0 + j < B.ng) {
-              sv += V(gv[j].x, gv[j].y, gv[j].z);
-              sw += V(gw[j].x, gw[j].y, gw[j].z);
-              sc += (int)gv[j].w;
-            }
-          }
-        }
-        dv = sv;
-        dw = sw;
-        cnt = sc;
-      }
+      // the exchange rows are free once the children's reactions have been read
+      if (LANES && nl > nb) lane_group_sums(X, lane, base, b, ty, B, dv, dw, cnt);
       // body-body contacts after the joint sums, where fewer values are live
       if (PAIRS && ty.np > 0) pair_phase(tab, t, *pl, X, lane, b, base, s, f, dv, dw, cnt, near0);
       if (TAPE) wtape_rest(tp, torque, cnt, lane);
@@ -524,63 +607,8 @@ __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const 
     if (live && b == 0) nonfinite[e] = ((bad >> base) & group) ? 1 : 0;
   }
   bool finished = false;
-  if (ENV) {
-    // reward and termination from the stepped state (the root's lane holds it)
-    const EnvT P = ea->env[t];
-    const int rl = base + P.root;
-    const float x0 = shfl(x_before, rl), x1 = shfl(s.p.x, rl), z1 = shfl(s.p.z, rl);
-    const bool healthy = z1 >= P.z_min && z1 <= P.z_max;
-    finished = !healthy;
-    // control cost: the squared actions as passed, summed over the
-    // environment's lanes in body order
-    float sq = 0.f;
-    for (int x = 0; x < MAXDOF; ++x) sq += raw_next[x] * raw_next[x];
-    float ctrl = 0.f;
-    for (int i = 0; i < nb; ++i) ctrl += shfl(sq, base + i);
-    if (live && b == P.root) {
-      ea->reward[e] = P.forward_weight * (x1 - x0) / ty.dt + (healthy ? P.healthy_reward : 0.f) - P.ctrl_cost * ctrl;
-      ea->done[e] = healthy ? 0 : 1;
-    }
-    // a finished environment continues from its reset state
-    if (finished && live) s = load_body(ea->reset, bs, e, Bm, E);
-    // observation of the final state: joint angles and relative angular
-    // velocity about each Euler axis on the child's lane (the parent's
-    // rotation and angular velocity read across lanes), the root's entries
-    // and the padding on the root's lane
-    const m3 Rf = quat_to_mat(s.q);
-    m3 RPf;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) RPf.m[i] = shfl(Rf.m[i], src_parent);
-    const v3 wP = V(shfl(s.w.x, src_parent), shfl(s.w.y, src_parent), shfl(s.w.z, src_parent));
-    const JointGeo g = joint_geo<MAXDOF>(J, RPf, joint_child<MAXDOF>(J, s, Rf));
-    const v3 wrel = s.w - wP;
-    const int D = ty.ndof;
-    if (live && has_joint && b < nb) {
-      for (int k = 0; k < MAXDOF; ++k) {
-        if (k < J.dof) {
-          ea->obs[(size_t)(11 + J.dof0 + k) * E + e] = g.th[k];
-          ea->obs[(size_t)(11 + D + J.dof0 + k) * E + e] = dot(wrel, g.ax[k]);
-        }
-      }
-    }
-    if (live && b == P.root) {
-      const float head[11] = {s.p.z, s.q.w, s.q.x, s.q.y, s.q.z, s.v.x, s.v.y, s.v.z, s.w.x, s.w.y, s.w.z};
-#pragma unroll
-      for (int k = 0; k < 11; ++k) ea->obs[(size_t)k * E + e] = head[k];
-      for (int k = 11 + 2 * D; k < ea->Omax; ++k) ea->obs[(size_t)k * E + e] = 0.f;
-    }
-  }
-  if (live && b < nb) {
-    store_body(out, 0, s, b, e, Bm, E);
-    // padded body slots of a smaller system are written as zeros (a finished
-    // environment's as its reset state's)
-    for (int pb = nb + b; pb < Bm; pb += nb) {
-      if (ENV && finished)
-        store_body(out, 0, load_body(ea->reset, pb, e, Bm, E), pb, e, Bm, E);
-      else
-        zero_body(out, pb, e, Bm, E);
-    }
-  }
+  if (ENV) finished = env_epilogue<MAXDOF>(*ea, t, ty, J, has_joint, src_parent, raw_next, x_before, live, b, bs, base, e, Bm, E, s);
+  if (live && b < nb) store_result(out, s, nb, b, e, Bm, E, ENV && finished, ENV ? ea->reset : out);
 }
 
 // ONE_AXIS: every type of the batch has joints of at most one axis, so only
@@ -685,6 +713,280 @@ __global__ __launch_bounds__(256) void k_fused_env(const Tables* __restrict__ ta
                                                nonfinite, nullptr, 0, w, n_work, X, pl, &ea);
 }
 
+// ------------------------------------------------------------------ fused path, two wavefronts per group
+// The fused step of one work item's environments on a block of two
+// wavefronts. Both hold every body's state (one lane per body, as above) and
+// advance it alike; each substep's work between the kinematic update and the
+// integrators is divided between them:
+//   wavefront 0: the parents' states, joints and actuators -> reactions;
+//   wavefront 1: the inverse world inertia, the gyroscopic torque, ground and
+//                body-body contacts -> velocity changes.
+// Their results cross through LDS mail rows, double-buffered by substep
+// parity, so that one barrier per substep is enough: a row is rewritten two
+// substeps later, after a barrier that its readers reach only once they have
+// used what they read. Both then gather the children's reactions and run the
+// integrators on the same values.
+// What it buys: the substep is one long chain of instructions per wavefront
+// (quadruped: 472 VALU, 581 issue slots and 723 quad-cycles with the stalls),
+// a SIMD issues at most one of a wavefront's instructions per quad-cycle, and
+// gfx950 issues VALU instructions of two resident wavefronts together when
+// their operands are VGPRs or literals (measured: add, mul, fma 4.7-5.4 cycles
+// each with one wavefront per SIMD and with two; with an SGPR operand, and for
+// compares, min/max, selects and transcendentals, 8.5-9.5 with two). A batch
+// that leaves SIMDs with one wavefront or none therefore runs the two halves
+// side by side.
+struct SplitRows {
+  XchRows xj;              // wavefront 0's exchange rows (parents' states)
+  float4 joint[2][65][3];  // per parity and lane: force on the child, minus the torque on the parent, torque on
+                           // the child (9 floats); row 64 stays zero, for lanes without an i-th child
+  float4 body[2][64][5];   // per parity and lane: Iwinv (6), gyroscopic torque (3), dv (3), dw (3), 1 / contacts
+};
+// wavefront 1 needs exchange rows of its own for contact lanes and body-body contacts
+static inline size_t split_lds(bool pairs, bool cl) {
+  return sizeof(SplitRows) + (pairs || cl ? sizeof(XchRows) : 0) + (pairs ? sizeof(PairLanes) : 0);
+}
+
+// ROLE: 0 the joint wavefront, 1 the contact wavefront. The other parameters
+// as for fused_run (two contact candidates per lane in registers).
+template <int ROLE, int MAXDOF, bool TAPE, bool PAIRS, bool ENV, bool CL, int REGC>
+__device__ __forceinline__ void split_run(const Tables* __restrict__ tab, const WaveWork& wk,
+                                          const int32_t* __restrict__ env_list, const int32_t* __restrict__ type_off,
+                                          int E, int Bm, const Fields& in, const Fields& out,
+                                          const float* __restrict__ acts, int Am, int T, int save_every,
+                                          const Fields& traj, uint8_t* nonfinite, float* __restrict__ tape, int smax,
+                                          int w, int n_work, SplitRows* L, XchRows* XC, PairLanes* pl,
+                                          const EnvArgs* ea) {
+  constexpr bool JOINT = ROLE == 0, CONTACT = ROLE == 1;
+  constexpr bool LANES = CL && !TAPE;
+  const int t = wk.type;
+  TypeT ty = tab->type[t];
+  const int nb = ty.nb;
+  const int nl = LANES ? ty.nl : nb;
+  const int lane = threadIdx.x & 63;
+  const int per_wave = 64 / nl;
+  const bool spare = lane >= per_wave * nl;  // shadows the first slot's lanes (see fused_run)
+  const int slot = spare ? 0 : lane / nl;
+  const int b = spare ? lane - per_wave * nl : lane - slot * nl;
+  const int base = slot * nl;
+  const bool live = !spare && slot < wk.count;
+  const int e = env_list[type_off[t] + wk.k0 + (live ? slot : 0)];
+  BodyT B = tab->body[t][b];
+  const int bs = LANES ? B.body_of : b;
+  const bool has_joint = B.joint >= 0;
+  JointT J = tab->joint[t][has_joint ? B.joint : 0];
+  const int src_parent = base + (has_joint ? J.parent : b);
+  const int cfirst = LANES ? B.l0 : B.c0;
+  const int n_con = LANES ? B.l1 - B.l0 : B.c1 - B.c0;
+  const int max_con = LANES ? ty.max_lc : ty.max_contacts;
+  ContactT Creg[REGC];
+  // constants in VGPRs: an SGPR operand keeps an instruction from issuing together with the other wavefront's
+  pin(ty.h);
+  pin3(ty.g);
+  pin(B.inv_m);
+  if (ty.frozen) {
+    pin3(B.free_p);
+    pin3(B.free_r);
+  }
+  if (JOINT) {
+    pin_joint<MAXDOF>(J, has_joint);
+  } else {
+    pin(ty.beta_h);
+    pin(ty.one_plus_e);
+    pin(ty.mu);
+    pin3(B.I);
+    pin3(B.Iinv);
+#pragma unroll
+    for (int k = 0; k < REGC; ++k) {
+      Creg[k] = tab->contact[t][cfirst + (n_con > k ? k : 0)];
+      pin3(Creg[k].l);
+      pin(Creg[k].rho);
+    }
+    if (PAIRS && ty.np > 0) pair_lanes_load(tab, t, pl, lane, nl);
+  }
+  const PairSlot0 ps0 = (CONTACT && PAIRS && ty.np > 0) ? pair_slot0(*pl, b, base) : PairSlot0{-1, lane, lane};
+  // mail rows of the children (the zero row where there is none)
+  int csrc[GATHER];
+#pragma unroll
+  for (int i = 0; i < GATHER; ++i) csrc[i] = i < B.nch ? base + (int)((B.ch_packed >> (4 * i)) & 15u) : 64;
+  if (JOINT && lane < 3) L->joint[0][64][lane] = L->joint[1][64][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+
+  Body s = load_body(in, bs, e, Bm, E);
+  const float x_before = s.p.x;
+  s.v = keep(s.v, B.free_p);
+  s.w = keep(s.w, B.free_r);
+  int n_save = 0;
+  float raw_next[3] = {0.f, 0.f, 0.f};
+  if (JOINT && has_joint && T > 0)
+    for (int x = 0; x < MAXDOF; ++x) raw_next[x] = act_raw(acts, J, x, e, E);
+  for (int step = 0; step < T; ++step) {
+    float a[3] = {0.f, 0.f, 0.f};
+    if (JOINT) {
+      for (int x = 0; x < MAXDOF; ++x) a[x] = clampf(raw_next[x], J.act_lo[x], J.act_hi[x]);
+      if (has_joint && step + 1 < T)
+        for (int x = 0; x < MAXDOF; ++x) raw_next[x] = act_raw(acts + (size_t)(step + 1) * Am * E, J, x, e, E);
+    }
+    auto substep = [&](int sub, auto parity) {
+      constexpr int par = decltype(parity)::value;
+      float* tp = TAPE ? tape + (((size_t)step * smax + sub) * n_work + w) * TAPE_N * 64 : nullptr;
+      if (CONTACT && TAPE) wtape_state(tp, s, lane);
+      kinematic_unmasked(s, ty.h);
+      v3 force, torque, gyro, dv = V(0.f, 0.f, 0.f), dw = V(0.f, 0.f, 0.f);
+      s3 Iwinv;
+      float inv_n = 0.f;
+      int cnt = 0;
+      float4(*mj)[3] = L->joint[par];
+      float4(*mb)[5] = L->body[par];
+      if (JOINT) {
+        xch_put_pvw(&L->xj, lane, s);
+        const m3 R = quat_to_mat(s.q);
+        xch_put_rot(&L->xj, lane, s.w.z, R);
+        Body P;
+        m3 RP;
+        xch_get_pvw_rot(&L->xj, src_parent, P, RP);
+        P.q = s.q;  // unused: the joint reads the parent's orientation as RP
+        const JointChild jc = joint_child<MAXDOF>(J, s, R);
+        const JointOut jo = joint_eval<MAXDOF>(J, P, RP, s, jc, a);
+        mj[lane][0] = make_float4(jo.fc.x, jo.fc.y, jo.fc.z, jo.tpn.x);
+        mj[lane][1] = make_float4(jo.tpn.y, jo.tpn.z, jo.tc.x, jo.tc.y);
+        *reinterpret_cast<float*>(&mj[lane][2]) = jo.tc.z;
+        force = jo.fc;
+        torque = jo.tc;
+      } else {
+        const m3 R = quat_to_mat(s.q);
+        int near0 = 0;
+        if (PAIRS && ty.np > 0) {
+          xch_put_pvw(XC, lane, s);
+          xch_put_rot(XC, lane, s.w.z, R);
+          near0 = pair_near0(XC, *pl, ps0);
+        }
+        const Frame f = derive_inv(B, R);
+        ground_contacts<REGC, REGC == 2 && (!CL || PAIRS)>(&tab->contact[t][cfirst], Creg, n_con, max_con, ty, B, s, f, dv,
+                                                          dw, cnt);
+        gyro = gyro_torque(B, s, f);
+        if (LANES && nl > nb) lane_group_sums(XC, lane, base, b, ty, B, dv, dw, cnt);
+        if (PAIRS && ty.np > 0) pair_phase(tab, t, *pl, XC, lane, b, base, s, f, dv, dw, cnt, near0);
+        inv_n = cnt > 0 ? 1.f / (float)cnt : 0.f;
+        Iwinv = f.Iwinv;
+        mb[lane][0] = make_float4(Iwinv.xx, Iwinv.yy, Iwinv.zz, Iwinv.xy);
+        mb[lane][1] = make_float4(Iwinv.xz, Iwinv.yz, gyro.x, gyro.y);
+        mb[lane][2] = make_float4(gyro.z, dv.x, dv.y, dv.z);
+        mb[lane][3] = make_float4(dw.x, dw.y, dw.z, inv_n);
+      }
+      block_exchange();
+      // the other wavefront's results and the children's reactions (a child's
+      // on its parent is the opposite of its force and tpn), all reads in
+      // flight together; N: at least the type's largest child count
+      auto combine = [&](auto nc) {
+        constexpr int N = decltype(nc)::value;
+        float4 c0[N + 1];
+        float2 c1[N + 1];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          c0[i] = mj[csrc[i]][0];
+          c1[i] = *reinterpret_cast<const float2*>(&mj[csrc[i]][1]);
+        }
+        if (JOINT) {
+          const float4 m0 = mb[lane][0], m1 = mb[lane][1], m2 = mb[lane][2], m3_ = mb[lane][3];
+          Iwinv = s3{m0.x, m0.y, m0.z, m0.w, m1.x, m1.y};
+          gyro = V(m1.z, m1.w, m2.x);
+          dv = V(m2.y, m2.z, m2.w);
+          dw = V(m3_.x, m3_.y, m3_.z);
+          inv_n = m3_.w;
+        } else {
+          const float4 j0 = mj[lane][0], j1 = mj[lane][1];
+          const float j2 = *reinterpret_cast<const float*>(&mj[lane][2]);
+          force = V(j0.x, j0.y, j0.z);
+          torque = V(j1.z, j1.w, j2);
+        }
+        force = sel(has_joint, force, V(0.f, 0.f, 0.f));
+        torque = sel(has_joint, torque, V(0.f, 0.f, 0.f));
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          force -= V(c0[i].x, c0[i].y, c0[i].z);
+          torque -= V(c0[i].w, c1[i].x, c1[i].y);
+        }
+      };
+      if (ty.max_children <= 2)
+        combine(std::integral_constant<int, 2>{});
+      else
+        combine(std::integral_constant<int, GATHER>{});
+      for (int i = GATHER; i < ty.max_children; ++i) {
+        const int src = i < B.nch ? base + (int)((B.ch_packed >> (4 * i)) & 15u) : 64;
+        const float4 x0 = mj[src][0];
+        const float2 x1 = *reinterpret_cast<const float2*>(&mj[src][1]);
+        force -= V(x0.x, x0.y, x0.z);
+        torque -= V(x0.w, x1.x, x1.y);
+      }
+      if (CONTACT && TAPE) wtape_rest(tp, torque, cnt, lane);
+      // without frozen axes in the type (wave-uniform) the integrators skip the masks
+      if (ty.frozen) {
+        potential_apply(B, ty, s, Iwinv, force, torque, gyro);
+        collision_apply(B, s, dv, dw, inv_n);
+      } else {
+        potential_apply<false>(B, ty, s, Iwinv, force, torque, gyro);
+        collision_apply<false>(B, s, dv, dw, inv_n);
+      }
+    };
+    // the mail rows' parity is that of the substep within the step
+    for (int sub = 0; sub < ty.substeps; sub += 2) {
+      substep(sub, std::integral_constant<int, 0>{});
+      if (sub + 1 < ty.substeps)
+        substep(sub + 1, std::integral_constant<int, 1>{});
+      else
+        block_exchange();  // an odd count: the next step starts on the rows just read
+    }
+    if (CONTACT && save_every > 0 && (step + 1) % save_every == 0) {
+      if (live && b < nb) store_snapshot(traj, (size_t)n_save, s, b, e, Bm, E);
+      ++n_save;
+    }
+  }
+  if (CONTACT) {
+    if (nonfinite) {
+      const unsigned long long bad = __ballot(live && !finite_body(s));
+      const unsigned long long group = (nb >= 64) ? ~0ull : ((1ull << nb) - 1ull);
+      if (live && b == 0) nonfinite[e] = ((bad >> base) & group) ? 1 : 0;
+    }
+    return;
+  }
+  bool finished = false;
+  if (ENV) finished = env_epilogue<MAXDOF>(*ea, t, ty, J, has_joint, src_parent, raw_next, x_before, live, b, bs, base, e, Bm, E, s);
+  if (live && b < nb) store_result(out, s, nb, b, e, Bm, E, ENV && finished, ENV ? ea->reset : out);
+}
+
+// One work item per block of two wavefronts (w is block-uniform: a block past
+// the list ends as a whole, before any barrier).
+template <bool ONE_AXIS, bool TAPE, bool PAIRS, bool ENV, bool CL, int REGC = REG_CONTACTS>
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(PAIRS ? 2 : 3))) void k_split(const Tables* __restrict__ tab, const WaveWork* __restrict__ work,
+                                               int n_work, const int32_t* __restrict__ env_list,
+                                               const int32_t* __restrict__ type_off, int E, int Bm, Fields in,
+                                               Fields out, const float* __restrict__ acts, int Am, int T,
+                                               int save_every, Fields traj, uint8_t* nonfinite, float* tape, int smax,
+                                               EnvArgs ea) {
+  extern __shared__ float4 split_lds_mem[];
+  const int w = xcd_block(blockIdx.x, gridDim.x);
+  if (w >= n_work) return;
+  const WaveWork wk = work[w];
+  SplitRows* L = reinterpret_cast<SplitRows*>(split_lds_mem);
+  XchRows* XC = reinterpret_cast<XchRows*>(L + 1);
+  PairLanes* pl = PAIRS ? reinterpret_cast<PairLanes*>(XC + 1) : nullptr;
+  const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#define BX_ROLE(R, D)                                                                                              \
+  split_run<R, D, TAPE, PAIRS, ENV, CL, REGC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every, traj, \
+                                        nonfinite, tape, smax, w, n_work, L, XC, pl, &ea)
+  if (ONE_AXIS || tab->type[wk.type].max_dof <= 1) {
+    if (role == 0)
+      BX_ROLE(0, 1);
+    else
+      BX_ROLE(1, 1);
+  } else {
+    if (role == 0)
+      BX_ROLE(0, 3);
+    else
+      BX_ROLE(1, 3);
+  }
+#undef BX_ROLE
+}
+
 // ------------------------------------------------------------------ small helpers
 __global__ void k_copy_state(int n3, int n4, Fields in, Fields out) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -699,6 +1001,16 @@ __global__ void k_copy_state(int n3, int n4, Fields in, Fields out) {
 static inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
 // ------------------------------------------------------------------ environment layer
+// Whether the two-wavefront kernels take a launch of n_work work items: up to
+// five per compute unit (1280 on 256), where both wavefronts of every item
+// are resident and the SIMDs have issue slots to spare. Measured, 20 steps,
+// one wavefront per item against two (us): quadruped 4096 (586 items) 258 ->
+// 197, 8192 (1171) 295 -> 281, 10240 (1463) 299 -> 320; biped 2048 (410) 265
+// -> 224, 6144 (1229) 313 -> 298, 8192 (1639) 320 -> 429. With body-body
+// contacts a block's LDS (42 KB) lets a compute unit hold three: grasp 4096
+// (683) 555 -> 502, 6144 (1024) 541 -> 771.
+static bool split_pays(const LaunchCtx& c, int n_work, bool pairs) { return n_work <= (pairs ? 3 : 5) * c.n_cu; }
+
 hipError_t launch_env_step(const LaunchCtx& c, const WaveWork* work, int n_work, int waves_per_block,
                            const EnvT* env, int Omax, Fields in, Fields out, const float* act, Fields reset, float* obs,
                            float* reward, uint8_t* done, bool flags, hipStream_t s) {
@@ -716,6 +1028,23 @@ hipError_t launch_env_step(const LaunchCtx& c, const WaveWork* work, int n_work,
 #define BX_ENV(P, R, L)                                                                                            \
   hipLaunchKernelGGL((k_fused_env<P, R, L>), grid, block, lds, s, c.tab, work, n_work, c.env_list, c.type_off, c.E, \
                      c.Bm, in, out, act, c.Am, nf, ea)
+  if (split_pays(c, n_work, pairs) && (cl || !many_contacts)) {
+    const dim3 sgrid(n_work), sblock(128);
+    const Fields none{nullptr, nullptr, nullptr, nullptr};
+#define BX_SPLIT(P, L)                                                                                             \
+  hipLaunchKernelGGL((k_split<false, false, P, true, L>), sgrid, sblock, split_lds(pairs, cl), s, c.tab, work, n_work, \
+                     c.env_list, c.type_off, c.E, c.Bm, in, out, act, c.Am, 1, 0, none, nf, nullptr, 0, ea)
+    if (pairs && cl)
+      BX_SPLIT(true, true);
+    else if (pairs)
+      BX_SPLIT(true, false);
+    else if (cl)
+      BX_SPLIT(false, true);
+    else
+      BX_SPLIT(false, false);
+#undef BX_SPLIT
+    return hipGetLastError();
+  }
   // with contact lanes, candidates past a lane's first two are read from the table
   if (pairs && cl)
     BX_ENV(true, REG_CONTACTS, true);
@@ -764,6 +1093,39 @@ hipError_t launch_fused(const LaunchCtx& c, const WaveWork* work, int n_work, in
   // (further ones, of a type whose lanes did not fit, are read from the table)
   if (cl) many_lane_contacts = false;
   const size_t lds = fused_lds_per_wave(pairs) * waves_per_block;
+  if (split_pays(c, n_work, pairs) && (tape || !many_lane_contacts)) {
+    const dim3 grid(n_work), block(128);
+    uint8_t* nf = flags ? c.nonfinite : nullptr;
+    const EnvArgs none{};
+    const size_t sl = split_lds(pairs, cl);
+#define BX_SPLIT(A, TP, P, ...)                                                                                       \
+  hipLaunchKernelGGL((k_split<A, TP, P, false, __VA_ARGS__>), grid, block, sl, s, c.tab, work, n_work, c.env_list, c.type_off, \
+                     c.E, c.Bm, in, out, acts, c.Am, T, save_every, traj, nf, tape, smax, none)
+    if (tape && pairs)
+      BX_SPLIT(false, true, true, false);
+    else if (tape && many_contacts)
+      BX_SPLIT(false, true, false, false, 8);
+    else if (tape)
+      BX_SPLIT(false, true, false, false);
+    else if (pairs && one_axis && cl)
+      BX_SPLIT(true, false, true, true);
+    else if (pairs && one_axis)
+      BX_SPLIT(true, false, true, false);
+    else if (pairs && cl)
+      BX_SPLIT(false, false, true, true);
+    else if (pairs)
+      BX_SPLIT(false, false, true, false);
+    else if (one_axis && cl)
+      BX_SPLIT(true, false, false, true);
+    else if (one_axis)
+      BX_SPLIT(true, false, false, false);
+    else if (cl)
+      BX_SPLIT(false, false, false, true);
+    else
+      BX_SPLIT(false, false, false, false);
+#undef BX_SPLIT
+    return hipGetLastError();
+  }
   if (pairs) {
     const dim3 grid(cdiv(n_work, waves_per_block)), block(64 * waves_per_block);
     uint8_t* nf = flags ? c.nonfinite : nullptr;

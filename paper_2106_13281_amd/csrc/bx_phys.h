@@ -146,16 +146,20 @@ struct Frame {
 // velocity; p += h v; q <- normalize(q + h/2 (0, w) (x) q).
 // The kinematic update for a state whose frozen velocity components are
 // already zero (the integrators below keep them zero).
+// The multiply-adds are written out: left to the compiler, which product of
+// a sum is fused depends on the code around, and kernels that have to agree bit
+// for bit on a state (the two wavefronts of the split step, and every kernel
+// that may run a batch) would not.
 BXF void kinematic_unmasked(Body& s, float h) {
-  s.p = s.p + h * s.v;
+  s.p = V(fmaf(h, s.v.x, s.p.x), fmaf(h, s.v.y, s.p.y), fmaf(h, s.v.z, s.p.z));
   // (0, w) (x) q written out: the product with a pure quaternion has no
   // terms in its zero real part
   const float hh = 0.5f * h;
   const v3 w = V(hh * s.w.x, hh * s.w.y, hh * s.w.z);
   const q4 a = s.q;
-  const q4 q{a.w - (w.x * a.x + w.y * a.y + w.z * a.z), a.x + (w.x * a.w + w.y * a.z - w.z * a.y),
-             a.y + (w.y * a.w - w.x * a.z + w.z * a.x), a.z + (w.z * a.w + w.x * a.y - w.y * a.x)};
-  float inv = 1.f / sqrtf(q.w * q.w + q.x * q.x + q.y * q.y + q.z * q.z);
+  const q4 q{a.w - fmaf(w.z, a.z, fmaf(w.y, a.y, w.x * a.x)), a.x + fmaf(-w.z, a.y, fmaf(w.y, a.z, w.x * a.w)),
+             a.y + fmaf(w.z, a.x, fmaf(w.y, a.w, -(w.x * a.z))), a.z + fmaf(-w.y, a.x, fmaf(w.x, a.y, w.z * a.w))};
+  float inv = 1.f / sqrtf(fmaf(q.z, q.z, fmaf(q.y, q.y, fmaf(q.w, q.w, q.x * q.x))));
   s.q = q4{q.w * inv, q.x * inv, q.y * inv, q.z * inv};
 }
 BXF void kinematic(const BodyT& B, Body& s, float h) {
@@ -392,14 +396,16 @@ BXF bool contact_eval(const ContactT& c, const TypeT& ty, const BodyT& B, const 
 // Potential integrator: v += h (g + f/m); w += h Iwinv (t - w x (Iw w)).
 // Iw w is formed in the body frame, R (I o (R^T w)), which needs no world
 // inertia matrix.
+BXF v3 gyro_torque(const BodyT& B, const Body& s, const Frame& f) {
+  v3 wb = mul_t(f.R, s.w);
+  return cross(s.w, mul(f.R, V(B.I[0] * wb.x, B.I[1] * wb.y, B.I[2] * wb.z)));
+}
 // MASKED = false: for a system type without frozen axes (the same result,
 // without the per-axis selects).
 template <bool MASKED = true>
-BXF void potential(const BodyT& B, const TypeT& ty, Body& s, const Frame& f, v3 force, v3 torque) {
+BXF void potential_apply(const BodyT& B, const TypeT& ty, Body& s, const s3& Iwinv, v3 force, v3 torque, v3 gyro) {
   v3 acc = ld3(ty.g) + B.inv_m * force;
-  v3 wb = mul_t(f.R, s.w);
-  v3 gyro = cross(s.w, mul(f.R, V(B.I[0] * wb.x, B.I[1] * wb.y, B.I[2] * wb.z)));
-  v3 alpha = mul(f.Iwinv, torque - gyro);
+  v3 alpha = mul(Iwinv, torque - gyro);
   if (MASKED) {
     s.v = keep_fma(s.v, ty.h, acc, B.free_p);
     s.w = keep_fma(s.w, ty.h, alpha, B.free_r);
@@ -408,21 +414,27 @@ BXF void potential(const BodyT& B, const TypeT& ty, Body& s, const Frame& f, v3 
     s.w = V(fmaf(ty.h, alpha.x, s.w.x), fmaf(ty.h, alpha.y, s.w.y), fmaf(ty.h, alpha.z, s.w.z));
   }
 }
+template <bool MASKED = true>
+BXF void potential(const BodyT& B, const TypeT& ty, Body& s, const Frame& f, v3 force, v3 torque) {
+  potential_apply<MASKED>(B, ty, s, f.Iwinv, force, torque, gyro_torque(B, s, f));
+}
 
 // Collision integrator: the body's contact impulses averaged over the n
-// candidates that applied one.
+// candidates that applied one; inv = 1 / n, and where n = 0 (no impulse:
+// dv = dw = 0) inv = 0 leaves the velocities as they are.
+template <bool MASKED = true>
+BXF void collision_apply(const BodyT& B, Body& s, v3 dv, v3 dw, float inv) {
+  if (MASKED) {
+    s.v = keep_fma(s.v, inv, dv, B.free_p);
+    s.w = keep_fma(s.w, inv, dw, B.free_r);
+  } else {
+    s.v = V(fmaf(inv, dv.x, s.v.x), fmaf(inv, dv.y, s.v.y), fmaf(inv, dv.z, s.v.z));
+    s.w = V(fmaf(inv, dw.x, s.w.x), fmaf(inv, dw.y, s.w.y), fmaf(inv, dw.z, s.w.z));
+  }
+}
 template <bool MASKED = true>
 BXF void collision(const BodyT& B, Body& s, v3 dv, v3 dw, int n) {
-  if (n > 0) {
-    float inv = 1.f / (float)n;
-    if (MASKED) {
-      s.v = keep_fma(s.v, inv, dv, B.free_p);
-      s.w = keep_fma(s.w, inv, dw, B.free_r);
-    } else {
-      s.v = V(fmaf(inv, dv.x, s.v.x), fmaf(inv, dv.y, s.v.y), fmaf(inv, dv.z, s.v.z));
-      s.w = V(fmaf(inv, dw.x, s.w.x), fmaf(inv, dw.y, s.w.y), fmaf(inv, dw.z, s.w.z));
-    }
-  }
+  if (n > 0) collision_apply<MASKED>(B, s, dv, dw, 1.f / (float)n);
 }
 
 BXF bool finite_body(const Body& s) {
