@@ -340,15 +340,20 @@ __device__ __forceinline__ void ground_contacts(const ContactT* __restrict__ C, 
     const float d0 = Creg[0].rho - (s.p.z + rl0.z), d1 = Creg[REGC - 1].rho - (s.p.z + rl1.z);
     const bool p0 = 0 < max_con && n_con > 0 && d0 > 0.f;
     const bool p1 = 1 < max_con && n_con > 1 && d1 > 0.f;
-    if (p0 || p1)
-      cnt += contact_apply(p0 ? Creg[0].rho : Creg[REGC - 1].rho, ty, B, s, f, sel(p0, rl0, rl1), p0 ? d0 : d1, dv, dw)
-                 ? 1
-                 : 0;
-    if (p0 && p1) cnt += contact_apply(Creg[REGC - 1].rho, ty, B, s, f, rl1, d1, dv, dw) ? 1 : 0;
+    if (__ballot(p0 || p1))
+      contact_add(p0 ? Creg[0].rho : Creg[REGC - 1].rho, ty, B, s, f.Iwinv, sel(p0, rl0, rl1), p0 ? d0 : d1, p0 || p1, dv,
+                  dw, cnt);
+    if (__ballot(p0 && p1)) contact_add(Creg[REGC - 1].rho, ty, B, s, f.Iwinv, rl1, d1, p0 && p1, dv, dw, cnt);
   } else {
 #pragma unroll
-    for (int k = 0; k < REGC; ++k)
-      if (k < max_con && n_con > k) cnt += contact_eval(Creg[k], ty, B, s, f, dv, dw) ? 1 : 0;
+    for (int k = 0; k < REGC; ++k) {
+      if (k < max_con) {
+        const v3 rl = mul(f.R, ld3(Creg[k].l));
+        const float depth = Creg[k].rho - (s.p.z + rl.z);
+        const bool in = n_con > k && depth > 0.f;
+        if (__ballot(in)) contact_add(Creg[k].rho, ty, B, s, f.Iwinv, rl, depth, in, dv, dw, cnt);
+      }
+    }
   }
   for (int c = REGC; c < n_con; ++c) cnt += contact_eval(C[c], ty, B, s, f, dv, dw) ? 1 : 0;
 }
