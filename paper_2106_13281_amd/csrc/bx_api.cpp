@@ -125,6 +125,7 @@ struct brax_sys {
     c.Am = Am;
     c.n_types = n_types;
     c.n_cu = n_cu;
+    c.lds_limit = lds_limit;
     c.env_type = d_env_type;
     c.env_list = d_env_list;
     c.type_off = d_type_off;

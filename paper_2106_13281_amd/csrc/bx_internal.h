@@ -89,6 +89,7 @@ struct LaunchCtx {
   int E, Bm, Am;
   int n_types;
   int n_cu;                     // compute units of the device
+  size_t lds_limit;             // LDS of one workgroup
   const int32_t* env_type;      // device [E]
   const int32_t* env_list;      // device, grouped by type
   const int32_t* type_off;      // device [n_types]

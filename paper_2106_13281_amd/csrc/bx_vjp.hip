@@ -23,6 +23,8 @@
 #include "bx_access.h"
 #include "bx_adj.h"
 #include "bx_pair_lanes.h"
+#include "bx_split.h"
+#include "bx_split_adj.h"
 #include "bx_vjp.h"
 
 namespace bx {
@@ -32,23 +34,6 @@ namespace {
 constexpr int TB = 256;
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
-__device__ __forceinline__ Bar load_bar(const Fields& f, int b, int e, int Bm, int E) {
-  Body s = load_body(f, b, e, Bm, E);
-  Bar r;
-  r.p = s.p;
-  r.q = s.q;
-  r.v = s.v;
-  r.w = s.w;
-  return r;
-}
-__device__ __forceinline__ void store_bar(const Fields& f, const Bar& r, int b, int e, int Bm, int E) {
-  Body s;
-  s.p = r.p;
-  s.q = r.q;
-  s.v = r.v;
-  s.w = r.w;
-  store_body(f, 0, s, b, e, Bm, E);
-}
 // 13-float bar in a [13 * N][n] slot array at item i, environment slot k
 __device__ __forceinline__ void slot_store_bar(float* sl, int x0, int N, int i, int n, int k, const Bar& r) {
   const float v[13] = {r.p.x, r.p.y, r.p.z, r.q.w, r.q.x, r.q.y, r.q.z, r.v.x, r.v.y, r.v.z, r.w.x, r.w.y, r.w.z};
@@ -629,6 +614,84 @@ __global__ __launch_bounds__(64) void k_fused_vjp_tape(const Tables* __restrict_
         nullptr, X, tape, w, n_work, nullptr, 0, pl, T, tstride);
 }
 
+// LDS of the forward and the adjoint rows, which take turns.
+constexpr size_t SPLIT_VJP_ROWS = sizeof(SplitRows) > sizeof(AdjRows) ? sizeof(SplitRows) : sizeof(AdjRows);
+
+// The adjoint of T consecutive steps from their tape on three wavefronts per
+// work item (one per block; see bx_split_adj.h).
+template <bool PAIRS, bool ONE_AXIS, int REGC>
+__global__ __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(PAIRS ? 1 : REGC > 2 ? 2 : 3))) void k_split_vjp_tape(
+    const Tables* __restrict__ tab, const WaveWork* __restrict__ work, int n_work, const int32_t* __restrict__ env_list,
+    const int32_t* __restrict__ type_off, int E, int Bm, int Am, const float* __restrict__ tape, size_t tstride, int T,
+    const float* __restrict__ act, Fields g_out, Fields g_in, float* __restrict__ g_act) {
+  extern __shared__ float4 split_lds_mem[];
+  const int w = xcd_block(blockIdx.x, gridDim.x);
+  if (w >= n_work) return;
+  const WaveWork wk = work[w];
+  AdjRows* L = reinterpret_cast<AdjRows*>(split_lds_mem);
+  PairLanes* pl = PAIRS ? reinterpret_cast<PairLanes*>(L + 1) : nullptr;
+  const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  auto rec_at = [&](int step, int sub) { return tape + step * tstride + ((size_t)sub * n_work + w) * TAPE_N * 64; };
+#define BX_ROLE(R, D)                                                                                              \
+  split_adj_run<R, D, PAIRS, REGC, true>(tab, wk, env_list, type_off, E, Bm, Am, act, g_out, g_in, g_act, T, rec_at, L, pl)
+  const bool one = ONE_AXIS || tab->type[wk.type].max_dof <= 1;
+  if (role == 0)
+    BX_ROLE(0, 1);
+  else if (role == 2)
+    BX_ROLE(2, 1);
+  else if (one)
+    BX_ROLE(1, 1);
+  else
+    BX_ROLE(1, 3);
+#undef BX_ROLE
+}
+
+// The adjoint of one step on three wavefronts per work item: the forward
+// substeps on two of them with their records in LDS, then the reverse ones.
+template <bool PAIRS, bool ONE_AXIS, int REGC>
+__global__ __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(PAIRS ? 1 : 2))) void k_split_vjp(
+    const Tables* __restrict__ tab, const WaveWork* __restrict__ work, int n_work, const int32_t* __restrict__ env_list,
+    const int32_t* __restrict__ type_off, int E, int Bm, int Am, Fields in, const float* __restrict__ act, Fields g_out,
+    Fields g_in, float* __restrict__ g_act) {
+  extern __shared__ float4 split_lds_mem[];  // [forward or adjoint rows] [exchange rows, body-body tables (PAIRS)] [tape]
+  const int w = xcd_block(blockIdx.x, gridDim.x);
+  if (w >= n_work) return;
+  const WaveWork wk = work[w];
+  SplitRows* L = reinterpret_cast<SplitRows*>(split_lds_mem);
+  XchRows* XC = reinterpret_cast<XchRows*>(reinterpret_cast<char*>(split_lds_mem) + SPLIT_VJP_ROWS);
+  PairLanes* pl = PAIRS ? reinterpret_cast<PairLanes*>(XC + 1) : nullptr;
+  float* tape = PAIRS ? reinterpret_cast<float*>(pl + 1) : reinterpret_cast<float*>(XC);
+  AdjRows* A = reinterpret_cast<AdjRows*>(split_lds_mem);
+  const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool one = ONE_AXIS || tab->type[wk.type].max_dof <= 1;
+#define BX_FWD(R, D) split_fwd_run<R, D, PAIRS, REGC>(tab, wk, env_list, type_off, E, Bm, in, act, tape, L, XC, pl)
+  if (role == 2) {
+    BX_FWD(1, 1);
+  } else if (role == 0) {
+    // one barrier per substep, as the other two
+    const int S = tab->type[wk.type].substeps;
+    for (int sub = 0; sub < S; ++sub) block_exchange();
+  } else if (one) {
+    BX_FWD(0, 1);
+  } else {
+    BX_FWD(0, 3);
+  }
+#undef BX_FWD
+  block_exchange();
+  auto rec_at = [&](int, int sub) { return tape + (size_t)sub * TAPE_N * 64; };
+#define BX_ROLE(R, D)                                                                                                \
+  split_adj_run<R, D, PAIRS, REGC, false>(tab, wk, env_list, type_off, E, Bm, Am, act, g_out, g_in, g_act, 1, rec_at, A, pl)
+  if (role == 0)
+    BX_ROLE(0, 1);
+  else if (role == 2)
+    BX_ROLE(2, 1);
+  else if (one)
+    BX_ROLE(1, 1);
+  else
+    BX_ROLE(1, 3);
+#undef BX_ROLE
+}
+
 // Whether a type of the batch has body-body contact candidates: the kernels
 // with the body-body phases are launched for such batches only.
 bool any_pairs(const LaunchCtx& c) {
@@ -636,6 +699,15 @@ bool any_pairs(const LaunchCtx& c) {
     if (c.host_tab->type[t].np > 0) return true;
   return false;
 }
+
+// Whether the three-wavefront adjoints take a launch of n_work work items:
+// always without body-body contacts. Measured, 10 steps from their tape, one
+// wavefront per item against three (us): quadruped 1024 (147 items) 281 ->
+// 139, 4096 (586) 307 -> 195, 12288 (1756) 600 -> 387; biped 1024 296 -> 124,
+// 8192 (1639) 593 -> 365; chain 12288 313 -> 189. The body-body adjoint's
+// registers leave room for one block on a compute unit: grasp 2048 (228 items)
+// 493 -> 358, 3072 (342) 507 -> 687.
+bool split_vjp_pays(const LaunchCtx& c, int n_work) { return !any_pairs(c) || n_work <= c.n_cu; }
 
 // Whether every type of the batch has joints of at most one axis: such
 // batches take the kernels compiled for that path alone (fewer registers).
@@ -671,6 +743,28 @@ bool many_contacts(const LaunchCtx& c) {
       hipLaunchKernelGGL((K<PAIRS, true, REG_CONTACTS>), __VA_ARGS__); \
     else                                                               \
       hipLaunchKernelGGL((K<PAIRS, false, REG_CONTACTS>), __VA_ARGS__); \
+  } while (0)
+
+// Launches kernel template K<PAIRS, ONE_AXIS, REGC> on blocks of three
+// wavefronts with `lds_` bytes of LDS. A batch with a body of many contacts holds eight candidates in registers here (they take
+// none from the joint's wavefront), so that a type's results do not depend on
+// the batch it is in.
+#define LAUNCH_SPLIT(K, lds_, ...)                                                     \
+  do {                                                                                 \
+    const bool one_ = all_one_axis(c), many_ = many_contacts(c);                       \
+    const dim3 grid_(sched.n_work), block_(192);                                       \
+    if (any_pairs(c) && one_)                                                          \
+      hipLaunchKernelGGL((K<true, true, 8>), grid_, block_, lds_, s, __VA_ARGS__);     \
+    else if (any_pairs(c))                                                             \
+      hipLaunchKernelGGL((K<true, false, 8>), grid_, block_, lds_, s, __VA_ARGS__);    \
+    else if (one_ && many_)                                                            \
+      hipLaunchKernelGGL((K<false, true, 8>), grid_, block_, lds_, s, __VA_ARGS__);    \
+    else if (one_)                                                                     \
+      hipLaunchKernelGGL((K<false, true, REG_CONTACTS>), grid_, block_, lds_, s, __VA_ARGS__); \
+    else if (many_)                                                                    \
+      hipLaunchKernelGGL((K<false, false, 8>), grid_, block_, lds_, s, __VA_ARGS__);   \
+    else                                                                               \
+      hipLaunchKernelGGL((K<false, false, REG_CONTACTS>), grid_, block_, lds_, s, __VA_ARGS__); \
   } while (0)
 
 size_t vjp_workspace_bytes(const Tables& tab, int n_types, const int* type_cnt, int E, int Bm) {
@@ -765,12 +859,15 @@ hipError_t launch_vjp_params(const LaunchCtx& c, const VjpSched& sched, Fields i
 hipError_t launch_vjp_tape(const LaunchCtx& c, const VjpSched& sched, const float* tape, size_t tstride, int T,
                            const float* act, Fields g_out, Fields g_in, float* g_act, hipStream_t s) {
   if (sched.n_work == 0 || T <= 0) return hipSuccess;
-  if (any_pairs(c))
-    LAUNCH_AXES(k_fused_vjp_tape, true, dim3(sched.n_work), dim3(64), sizeof(XchRows) + sizeof(PairLanes), s, c.tab, sched.work,
-                sched.n_work, c.env_list, c.type_off, c.E, c.Bm, c.Am, tape, tstride, T, act, g_out, g_in, g_act);
-  else
-    LAUNCH_AXES(k_fused_vjp_tape, false, dim3(sched.n_work), dim3(64), sizeof(XchRows), s, c.tab, sched.work, sched.n_work,
-                c.env_list, c.type_off, c.E, c.Bm, c.Am, tape, tstride, T, act, g_out, g_in, g_act);
+  if (split_vjp_pays(c, sched.n_work)) {
+    const size_t lds = sizeof(AdjRows) + (any_pairs(c) ? sizeof(PairLanes) : 0);
+    LAUNCH_SPLIT(k_split_vjp_tape, lds, c.tab, sched.work, sched.n_work, c.env_list, c.type_off, c.E, c.Bm, c.Am, tape,
+                 tstride, T, act, g_out, g_in, g_act);
+  } else {
+    LAUNCH_AXES(k_fused_vjp_tape, true, dim3(sched.n_work), dim3(64), sizeof(XchRows) + sizeof(PairLanes), s, c.tab,
+                sched.work, sched.n_work, c.env_list, c.type_off, c.E, c.Bm, c.Am, tape, tstride, T, act, g_out, g_in,
+                g_act);
+  }
   return hipGetLastError();
 }
 
@@ -794,6 +891,13 @@ hipError_t launch_vjp(const LaunchCtx& c, VjpWork& w, const VjpSched& sched, Fie
     // one wavefront per block; its tape lives in LDS
     const size_t lds = sizeof(XchRows) + smax * TAPE_N * 64 * sizeof(float);
     if (sched.n_work == 0) return hipSuccess;
+    const size_t split = SPLIT_VJP_ROWS + smax * TAPE_N * 64 * sizeof(float) +
+                         (any_pairs(c) ? sizeof(XchRows) + sizeof(PairLanes) : 0);
+    if (split_vjp_pays(c, sched.n_work) && split <= c.lds_limit) {
+      LAUNCH_SPLIT(k_split_vjp, split, c.tab, sched.work, sched.n_work, c.env_list, c.type_off, E, Bm, c.Am, in, act, g_out,
+                   g_in, g_act);
+      return hipGetLastError();
+    }
     if (any_pairs(c))
       LAUNCH_AXES(k_fused_vjp, true, dim3(sched.n_work), dim3(64), lds + sizeof(PairLanes), s, c.tab, sched.work,
                   sched.n_work, c.env_list, c.type_off, E, Bm, c.Am, (int)smax, in, act, g_out, g_in, g_act);
