@@ -54,34 +54,56 @@ __device__ __forceinline__ void zero_body(const Fields& f, int b, int e, int Bm,
   store_body(f, 0, z, b, e, Bm, E);
 }
 
-// Tape of the fused path, wavefront-major: per substep and work item, TAPE_N
-// rows of 64 floats (one per lane; rows 0-12 the state before the kinematic
-// update, 13-15 the total torque, 16 the applied-contact count), so that
-// every store and load of a row is 256 contiguous bytes.
+// Tape of the fused path, wavefront-major: per substep and work item a record
+// of TAPE_N x 64 floats: four rows of 64 lanes x 4 floats (the state before the
+// kinematic update, 13, then the total torque, 3) and one of 64 (the
+// applied-contact count), so that a record takes five stores or loads, each of
+// contiguous bytes. GLOBAL: device memory, where the caller's tape may be
+// aligned to 4 bytes only; else LDS.
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
+template <bool GLOBAL>
+__device__ __forceinline__ void wtape_row(float* tp, int row, int lane, f4 v) {
+  float* q = tp + (row * 64 + lane) * 4;
+  if (GLOBAL)
+    *reinterpret_cast<f4_any*>(q) = v;
+  else
+    *reinterpret_cast<f4*>(q) = v;
+}
+template <bool GLOBAL>
 __device__ __forceinline__ void wtape_state(float* tp, const Body& s, int lane) {
-  const float v[13] = {s.p.x, s.p.y, s.p.z, s.q.w, s.q.x, s.q.y, s.q.z, s.v.x, s.v.y, s.v.z, s.w.x, s.w.y, s.w.z};
+  wtape_row<GLOBAL>(tp, 0, lane, f4{s.p.x, s.p.y, s.p.z, s.q.w});
+  wtape_row<GLOBAL>(tp, 1, lane, f4{s.q.x, s.q.y, s.q.z, s.v.x});
+  wtape_row<GLOBAL>(tp, 2, lane, f4{s.v.y, s.v.z, s.w.x, s.w.y});
+}
+// wz: the last component of the state before the kinematic update
+template <bool GLOBAL>
+__device__ __forceinline__ void wtape_torque(float* tp, float wz, v3 torque, int lane) {
+  wtape_row<GLOBAL>(tp, 3, lane, f4{wz, torque.x, torque.y, torque.z});
+}
+__device__ __forceinline__ void wtape_count(float* tp, int cnt, int lane) { tp[16 * 64 + lane] = (float)cnt; }
+// one record into registers (issued ahead of use by the adjoint, so that the
+// load's latency overlaps the substep before it)
+struct TapeRec {
+  f4 r[4];
+  float n;
+};
+template <bool GLOBAL>
+__device__ __forceinline__ void wtape_fetch(const float* tp, int lane, TapeRec& v) {
 #pragma unroll
-  for (int k = 0; k < 13; ++k) tp[k * 64 + lane] = v[k];
+  for (int k = 0; k < 4; ++k) {
+    const float* q = tp + (k * 64 + lane) * 4;
+    v.r[k] = GLOBAL ? f4(*reinterpret_cast<const f4_any*>(q)) : *reinterpret_cast<const f4*>(q);
+  }
+  v.n = tp[16 * 64 + lane];
 }
-__device__ __forceinline__ void wtape_rest(float* tp, v3 torque, int cnt, int lane) {
-  tp[13 * 64 + lane] = torque.x;
-  tp[14 * 64 + lane] = torque.y;
-  tp[15 * 64 + lane] = torque.z;
-  tp[16 * 64 + lane] = (float)cnt;
-}
-// one record's rows into registers (issued ahead of use by the adjoint, so
-// that the load's latency overlaps the substep before it)
-__device__ __forceinline__ void wtape_fetch(const float* tp, int lane, float (&v)[17]) {
-#pragma unroll
-  for (int k = 0; k < 17; ++k) v[k] = tp[k * 64 + lane];
-}
-__device__ __forceinline__ void wtape_unpack(const float (&v)[17], Body& s, v3& torque, int& cnt) {
-  s.p = V(v[0], v[1], v[2]);
-  s.q = q4{v[3], v[4], v[5], v[6]};
-  s.v = V(v[7], v[8], v[9]);
-  s.w = V(v[10], v[11], v[12]);
-  torque = V(v[13], v[14], v[15]);
-  cnt = (int)v[16];
+__device__ __forceinline__ void wtape_unpack(const TapeRec& v, Body& s, v3& torque, int& cnt) {
+  s.p = V(v.r[0].x, v.r[0].y, v.r[0].z);
+  s.q = q4{v.r[0].w, v.r[1].x, v.r[1].y, v.r[1].z};
+  s.v = V(v.r[1].w, v.r[2].x, v.r[2].y);
+  s.w = V(v.r[2].z, v.r[2].w, v.r[3].x);
+  torque = V(v.r[3].y, v.r[3].z, v.r[3].w);
+  cnt = (int)v.n;
 }
 
 // Blocks are dispatched round-robin over the 8 XCDs (each with its own L2):

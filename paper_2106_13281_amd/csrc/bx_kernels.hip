@@ -391,7 +391,7 @@ __device__ __forceinline__ void store_result(const Fields& out, const Body& s, i
 
 // TAPE: also write each substep's tape record (state before the kinematic
 // update, total torque, count of applied contacts) to the wavefront-major
-// tape[step][sub][work item w of n_work][TAPE_N][64], for the adjoint that
+// tape[step][sub][work item w of n_work][TAPE_N x 64], for the adjoint that
 // reads it instead of recomputing the step.
 // REGC: contact candidates of a body kept in registers (the rest are read
 // from the table inside the loop).
@@ -461,7 +461,8 @@ __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const 
       for (int x = 0; x < MAXDOF; ++x) raw_next[x] = act_raw(acts + (size_t)(step + 1) * Am * E, J, x, e, E);
     for (int sub = 0; sub < ty.substeps; ++sub) {
       float* tp = TAPE ? tape + (((size_t)step * smax + sub) * n_work + w) * TAPE_N * 64 : nullptr;
-      if (TAPE) wtape_state(tp, s, lane);
+      const float wz = s.w.z;
+      if (TAPE) wtape_state<true>(tp, s, lane);
       kinematic_unmasked(s, h);
       // parent's post-kinematic state through the exchange rows: this body's
       // state is written first and its rotation formed while that is in
@@ -520,7 +521,10 @@ __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const 
       if (LANES && nl > nb) lane_group_sums(X, lane, base, b, ty, B, dv, dw, cnt);
       // body-body contacts after the joint sums, where fewer values are live
       if (PAIRS && ty.np > 0) pair_phase(tab, t, *pl, X, lane, b, base, s, f, dv, dw, cnt, near0);
-      if (TAPE) wtape_rest(tp, torque, cnt, lane);
+      if (TAPE) {
+        wtape_torque<true>(tp, wz, torque, lane);
+        wtape_count(tp, cnt, lane);
+      }
       // without frozen axes in the type (wave-uniform) the integrators skip the masks
       if (ty.frozen) {
         potential(B, ty, s, f, force, torque);
@@ -661,6 +665,7 @@ __device__ __forceinline__ void split_run(const Tables* __restrict__ tab, const 
                                           const EnvArgs* ea) {
   constexpr bool JOINT = ROLE == 0, CONTACT = ROLE == 1;
   constexpr bool LANES = CL && !TAPE;
+  constexpr bool RECORD = TAPE && ROLE == tape_role(MAXDOF);
   const int t = wk.type;
   TypeT ty = tab->type[t];
   const int nb = ty.nb;
@@ -730,13 +735,15 @@ __device__ __forceinline__ void split_run(const Tables* __restrict__ tab, const 
     }
     auto substep = [&](int sub, auto parity) {
       float* tp = TAPE ? tape + (((size_t)step * smax + sub) * n_work + w) * TAPE_N * 64 : nullptr;
-      if (CONTACT && TAPE) wtape_state(tp, s, lane);
+      const float wz = s.w.z;
+      if (RECORD) wtape_state<true>(tp, s, lane);
       v3 torque;
       int cnt;
       split_substep<ROLE, MAXDOF, PAIRS, CL, REGC, decltype(parity)::value>(tab, t, ty, B, J, has_joint, Creg, cfirst, n_con,
                                                                             max_con, lane, b, base, nl > nb, src_parent, csrc,
                                                                             a, s, L, XC, pl, ps0, torque, cnt);
-      if (CONTACT && TAPE) wtape_rest(tp, torque, cnt, lane);
+      if (RECORD) wtape_torque<true>(tp, wz, torque, lane);
+      if (CONTACT && TAPE) wtape_count(tp, cnt, lane);
     };
     // the mail rows' parity is that of the substep within the step
     for (int sub = 0; sub < ty.substeps; sub += 2) {

@@ -111,6 +111,9 @@ static inline size_t split_lds(bool pairs, bool cl) {
   return sizeof(SplitRows) + (pairs || cl ? sizeof(XchRows) : 0) + (pairs ? sizeof(PairLanes) : 0);
 }
 
+// The wavefront that writes a substep's tape record (but for the contact
+// count): the one with less to do, the contact half beside three-axis joints.
+constexpr int tape_role(int maxdof) { return maxdof > 1 ? 1 : 0; }
 
 // One substep of the split step on one of its wavefronts (ROLE 0: joints, 1:
 // contacts); advances s. PAR: the mail rows' parity; two consecutive substeps

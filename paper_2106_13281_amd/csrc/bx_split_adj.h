@@ -72,8 +72,8 @@ __device__ __forceinline__ void pin(JointTan<MAXDOF>& k) {
   }
 }
 // The reverse substeps of T steps on one of the three wavefronts (ROLE 0:
-// body, 1: joint, 2: contact). rec(step, sub): the tape record of a substep
-// (17 rows of rstride floats apart, lane fastest). act, g_act [T][Am][E].
+// body, 1: joint, 2: contact). rec_at(step, sub): the tape record of a substep.
+// act, g_act [T][Am][E].
 // WARM: the records come from device memory (else from LDS).
 template <int ROLE, int MAXDOF, bool PAIRS, int REGC, bool WARM, class Rec>
 __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, const WaveWork& wk,
@@ -127,22 +127,15 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
   if (JOINT && lane < 5) L->joint[64][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
 
   if (BODY) {
-    float rec[17];
-    auto fetch = [&](int step, int sub) {
-      const float* r = rec_at(step, sub) + lane;
-#pragma unroll
-      for (int k = 0; k < 17; ++k) rec[k] = r[k * 64];
-    };
+    TapeRec rec;
+    auto fetch = [&](int step, int sub) { wtape_fetch<WARM>(rec_at(step, sub), lane, rec); };
     // the substep in rec: what this wavefront needs of it, and the frame row
     // of the others; then the record of the substep before it
     auto advance = [&](int step, int sub) {
       Body post;
-      post.p = V(rec[0], rec[1], rec[2]);
-      post.q = q4{rec[3], rec[4], rec[5], rec[6]};
-      post.v = V(rec[7], rec[8], rec[9]);
-      post.w = V(rec[10], rec[11], rec[12]);
-      const v3 ttot = V(rec[13], rec[14], rec[15]);
-      const int n = (int)rec[16];
+      v3 ttot;
+      int n;
+      wtape_unpack(rec, post, ttot, n);
       if (sub > 0)
         fetch(step, sub - 1);
       else if (step > 0)
@@ -344,14 +337,14 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
 
 // The forward substeps of one step before its adjoint, on wavefronts 1 (the
 // joint half of the split step, ROLE 0 there) and 2 (the contact half, ROLE 1),
-// their records into LDS (17 rows of 64 floats per substep).
+// their records into LDS.
 template <int ROLE, int MAXDOF, bool PAIRS, int REGC>
 __device__ __forceinline__ void split_fwd_run(const Tables* __restrict__ tab, const WaveWork& wk,
                                               const int32_t* __restrict__ env_list,
                                               const int32_t* __restrict__ type_off, int E, int Bm, const Fields& in,
                                               const float* __restrict__ act, float* lds_tape, SplitRows* L, XchRows* XC,
                                               PairLanes* pl) {
-  constexpr bool JOINT = ROLE == 0, CONTACT = ROLE == 1;
+  constexpr bool JOINT = ROLE == 0, CONTACT = ROLE == 1, RECORD = ROLE == tape_role(MAXDOF);
   const int t = wk.type;
   TypeT ty = tab->type[t];
   const int nb = ty.nb;
@@ -385,14 +378,16 @@ __device__ __forceinline__ void split_fwd_run(const Tables* __restrict__ tab, co
   s.w = keep(s.w, B.free_r);
   auto substep = [&](int sub, auto parity) {
     float* tp = lds_tape + (size_t)sub * TAPE_N * 64;
-    if (CONTACT) wtape_state(tp, s, lane);
+    const float wz = s.w.z;
+    if (RECORD) wtape_state<false>(tp, s, lane);
     v3 torque;
     int cnt;
     split_substep<ROLE, MAXDOF, PAIRS, false, REGC, decltype(parity)::value>(tab, t, ty, B, J, has_joint, Creg, B.c0, n_con,
                                                                              ty.max_contacts, lane, b, base, false,
                                                                              src_parent, csrc, a, s, L, XC, pl, ps0,
                                                                              torque, cnt);
-    if (CONTACT) wtape_rest(tp, torque, cnt, lane);
+    if (RECORD) wtape_torque<false>(tp, wz, torque, lane);
+    if (CONTACT) wtape_count(tp, cnt, lane);
   };
   for (int sub = 0; sub < ty.substeps; sub += 2) {
     substep(sub, std::integral_constant<int, 0>{});

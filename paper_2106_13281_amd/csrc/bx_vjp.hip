@@ -397,8 +397,8 @@ __device__ __forceinline__ void fused_vjp_run(const Tables* __restrict__ tab, co
   auto rec_at = [&](int step, int sub) {
     return hbm_tape + step * tstride + ((size_t)sub * n_work + w) * TAPE_N * 64;
   };
-  float rec[17];
-  if (FROM_TAPE) wtape_fetch(rec_at(T - 1, ty.substeps - 1), lane, rec);
+  TapeRec rec;
+  if (FROM_TAPE) wtape_fetch<true>(rec_at(T - 1, ty.substeps - 1), lane, rec);
   for (int step = T - 1; step >= 0; --step) {
     // the previous step's actions, loaded while this one is differentiated
     float raw_prev[3] = {0.f, 0.f, 0.f};
@@ -412,9 +412,9 @@ __device__ __forceinline__ void fused_vjp_run(const Tables* __restrict__ tab, co
       if (FROM_TAPE) {
         wtape_unpack(rec, pre, ttot, n);
         if (sub > 0)
-          wtape_fetch(rec_at(step, sub - 1), lane, rec);
+          wtape_fetch<true>(rec_at(step, sub - 1), lane, rec);
         else if (step > 0)
-          wtape_fetch(rec_at(step - 1, ty.substeps - 1), lane, rec);
+          wtape_fetch<true>(rec_at(step - 1, ty.substeps - 1), lane, rec);
       } else {
         const float* tp = lds + sub * TN * 64 + lane;
         if (PARAMS) ftot = V(tp[1088], tp[1152], tp[1216]);
@@ -665,8 +665,10 @@ __global__ __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(PAIRS ? 1 :
   const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool one = ONE_AXIS || tab->type[wk.type].max_dof <= 1;
 #define BX_FWD(R, D) split_fwd_run<R, D, PAIRS, REGC>(tab, wk, env_list, type_off, E, Bm, in, act, tape, L, XC, pl)
-  if (role == 2) {
+  if (role == 2 && one) {
     BX_FWD(1, 1);
+  } else if (role == 2) {
+    BX_FWD(1, 3);
   } else if (role == 0) {
     // one barrier per substep, as the other two
     const int S = tab->type[wk.type].substeps;
