@@ -553,8 +553,14 @@ __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const 
 // that path is compiled in (fewer registers). REGC: contact candidates per
 // body held in registers (8 for batches with a body of more than two, such
 // as a box's eight corners; 2 otherwise, where more registers only cost).
+// Three wavefronts per SIMD (168 registers, a few spilled) for one-axis
+// batches with two candidates: a batch too large for the split step is bound
+// by how many wavefronts hide one another's latency (quadruped x 20 steps, two
+// -> three per SIMD: 16384 environments 529 -> 415 us, 65536 1418 -> 1200;
+// manipulator 65536 1837 -> 1551). With three-axis joints the spills cost more
+// (biped 16384 599 -> 728).
 template <bool ONE_AXIS, int REGC, bool CL>
-__global__ __launch_bounds__(256) void k_fused(const Tables* __restrict__ tab, const WaveWork* __restrict__ work,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ONE_AXIS && REGC == REG_CONTACTS ? 3 : 2))) void k_fused(const Tables* __restrict__ tab, const WaveWork* __restrict__ work,
                                                int n_work, const int32_t* __restrict__ env_list,
                                                const int32_t* __restrict__ type_off, int E, int Bm, Fields in,
                                                Fields out, const float* __restrict__ acts, int Am, int T,
