@@ -556,7 +556,7 @@ __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const 
 // Three wavefronts per SIMD (168 registers, a few spilled) for one-axis
 // batches with two candidates: a batch too large for the split step is bound
 // by how many wavefronts hide one another's latency (quadruped x 20 steps, two
-// -> three per SIMD: 16384 environments 529 -> 415 us, 65536 1418 -> 1200;
+// -> three per SIMD: 16384 environments 529 -> 413-417 us, 65536 1418 -> 1188-1224;
 // manipulator 65536 1837 -> 1551). With three-axis joints the spills cost more
 // (biped 16384 599 -> 728).
 template <bool ONE_AXIS, int REGC, bool CL>
