@@ -205,18 +205,6 @@ __device__ __forceinline__ void pin(v3& a) {
   pin(a.y);
   pin(a.z);
 }
-__device__ __forceinline__ void pin(m3& a) {
-#pragma unroll
-  for (int i = 0; i < 9; ++i) pin(a.m[i]);
-}
-__device__ __forceinline__ void pin(s3& a) {
-  pin(a.xx);
-  pin(a.yy);
-  pin(a.zz);
-  pin(a.xy);
-  pin(a.xz);
-  pin(a.yz);
-}
 
 // contact_apply (the same values) without branches, for the lanes of a
 // wavefront together: a lane whose candidate does not penetrate (in = false)

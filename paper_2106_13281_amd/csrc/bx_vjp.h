@@ -50,7 +50,7 @@ hipError_t launch_vjp(const LaunchCtx& c, VjpWork& w, const VjpSched& sched, Fie
 hipError_t launch_vjp_params(const LaunchCtx& c, const VjpSched& sched, Fields in, const float* act, Fields g_out,
                              Fields g_in, float* g_act, float* g_params, int p_max, hipStream_t s);
 // The same adjoint, over T consecutive steps (the last first), from their
-// wavefront-major forward tape [T][Smax][n_work][TAPE_N][64] (tstride floats
+// wavefront-major forward tape [T][Smax][n_work][TAPE_N x 64] (tstride floats
 // per step; written by the fused forward with the same work list), without
 // recomputing the steps: act and g_act [T][Am][E].
 hipError_t launch_vjp_tape(const LaunchCtx& c, const VjpSched& sched, const float* tape, size_t tstride, int T,

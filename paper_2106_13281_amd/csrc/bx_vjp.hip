@@ -15,6 +15,12 @@
 //                 substep's input state
 //    Per-joint/contact results go to fixed slots; the gather order is fixed,
 //    so the result is deterministic.
+//
+// The fused adjoints run 1 and 2 in one launch, or 2 alone from a tape in
+// device memory: on three wavefronts per work item (bx_split_adj.h; the rule
+// is split_vjp_pays), or on one (fused_vjp_run) for parameter cotangents, for
+// body-body batches with more work items than CUs, and where the on-chip tape
+// leaves no room for the three wavefronts' rows.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -264,7 +270,7 @@ __global__ void k_adj_kinematic(const Tables* __restrict__ tab, int t, const int
 // by the parent lane in child order.
 
 // FROM_TAPE: the forward substeps are not recomputed; their tape records are
-// read from the wavefront-major hbm_tape[step][sub][work item w of n_work][TAPE_N][64]
+// read from the wavefront-major hbm_tape[step][sub][work item w of n_work][TAPE_N x 64]
 // (written by the fused forward with a tape, same work list; tstride floats
 // per step) instead of the LDS tape, and T consecutive steps are
 // differentiated in reverse in one pass (act and g_act [T][Am][E]), the
@@ -734,8 +740,9 @@ bool many_contacts(const LaunchCtx& c) {
 // the batch (`c` in scope); the remaining arguments are hipLaunchKernelGGL's.
 // Eight contact candidates are held in registers only for one-axis batches:
 // with three-axis joints the adjoint already fills the registers and the six
-// more candidates spill (a mixed batch's segment adjoint measured 774 us with
-// eight, 626 us with two), while a one-axis manipulator gains (388 -> 346 us).
+// more candidates spill (a mixed batch's one-wavefront segment adjoint measured
+// 774 us with eight, 626 us with two), while a one-axis manipulator gains (388
+// -> 346 us).
 #define LAUNCH_AXES(K, PAIRS, ...)                                     \
   do {                                                                 \
     const bool one_ = all_one_axis(c);                                 \
@@ -748,9 +755,9 @@ bool many_contacts(const LaunchCtx& c) {
   } while (0)
 
 // Launches kernel template K<PAIRS, ONE_AXIS, REGC> on blocks of three
-// wavefronts with `lds_` bytes of LDS. A batch with a body of many contacts holds eight candidates in registers here (they take
-// none from the joint's wavefront), so that a type's results do not depend on
-// the batch it is in.
+// wavefronts with `lds_` bytes of LDS. A batch with a body of many contacts
+// holds eight candidates in registers here (they take none from the joint's
+// wavefront), so that a type's results do not depend on the batch it is in.
 #define LAUNCH_SPLIT(K, lds_, ...)                                                     \
   do {                                                                                 \
     const bool one_ = all_one_axis(c), many_ = many_contacts(c);                       \
