@@ -15,9 +15,9 @@
 //            and frame of the next        parent's and the child's
 //            substep from its record      cotangents
 // Results cross through LDS rows written in one phase and read in the next.
-// One wavefront runs all of it as one chain; a batch of 1024 environments
-// leaves most SIMDs empty, so the three share the chain between SIMDs: gradient
-// of 1024 quadrupeds x 100 steps, forward and adjoint, 3.67 -> 2.22 ms.
+// One wavefront runs all of it as one chain; a small batch leaves most SIMDs
+// empty, so the three share the chain between SIMDs: single-step adjoint of
+// 700 quadrupeds, forward recompute included, 42.2 -> 24.2 us.
 #pragma once
 #include "bx_access.h"
 #include "bx_adj_tan.h"
@@ -75,8 +75,7 @@ __device__ __forceinline__ void pin(JointTan<MAXDOF>& k) {
 // The reverse substeps of T steps on one of the three wavefronts (ROLE 0:
 // body, 1: joint, 2: contact). rec_at(step, sub): the tape record of a substep.
 // act, g_act [T][Am][E].
-// WARM: the records come from device memory (else from LDS).
-template <int ROLE, int MAXDOF, bool PAIRS, int REGC, bool WARM, class Rec>
+template <int ROLE, int MAXDOF, bool PAIRS, int REGC, class Rec>
 __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, const WaveWork& wk,
                                               const int32_t* __restrict__ env_list,
                                               const int32_t* __restrict__ type_off, int E, int Bm, int Am,
@@ -129,7 +128,7 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
 
   if (BODY) {
     TapeRec rec;
-    auto fetch = [&](int step, int sub) { wtape_fetch<WARM>(rec_at(step, sub), lane, rec); };
+    auto fetch = [&](int step, int sub) { wtape_fetch<false>(rec_at(step, sub), lane, rec); };
     // the substep in rec: what this wavefront needs of it, and the frame row
     // of the others; then the record of the substep before it
     auto advance = [&](int step, int sub) {
@@ -237,21 +236,6 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
     R = m3{{r2.y, r2.z, r2.w, r3.x, r3.y, r3.z, r3.w, r4.x, r4.y}};
     return r4;
   };
-  // one load over the record three substeps on, so that the loads of its rows
-  // find it in the L2: from device memory they take longer than the substep
-  // they are issued ahead (wavefront 0 waited 500 of a substep's 3500 cycles)
-  int wstep = T - 1, wsub = S - 1;
-  float warm = 0.f;
-  auto warm_next = [&] {
-    pin(warm);
-    if (wstep >= 0 && lane < TAPE_N * 2) warm = rec_at(wstep, wsub)[lane * 32];
-    if (--wsub < 0) {
-      wsub = S - 1;
-      --wstep;
-    }
-  };
-  if (CONTACT && WARM)
-    for (int i = 0; i < 4; ++i) warm_next();
   block_exchange();
   for (int step = T - 1; step >= 0; --step) {
     float raw_prev[3] = {0.f, 0.f, 0.f}, ga[3] = {0.f, 0.f, 0.f};
@@ -313,7 +297,6 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
         }
         tbar_put(L->contact[lane], r);
       }
-      if (CONTACT && WARM) warm_next();
       block_exchange();
     }
     if (JOINT) {

@@ -16,11 +16,11 @@
 //    Per-joint/contact results go to fixed slots; the gather order is fixed,
 //    so the result is deterministic.
 //
-// The fused adjoints run 1 and 2 in one launch, or 2 alone from a tape in
-// device memory: on three wavefronts per work item (bx_split_adj.h; the rule
-// is split_vjp_pays), or on one (fused_vjp_run) for parameter cotangents, for
-// body-body batches with more work items than CUs, and where the on-chip tape
-// leaves no room for the three wavefronts' rows.
+// The fused adjoints run 1 and 2 in one launch, on three wavefronts per work
+// item (bx_split_adj.h; the rule is split_vjp_pays) or on one (fused_vjp_run):
+// for parameter cotangents, for body-body batches with more work items than
+// CUs, and where the on-chip tape leaves no room for the three wavefronts'
+// rows; 2 alone, from a tape in device memory, runs on one.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -623,35 +623,6 @@ __global__ __launch_bounds__(64) void k_fused_vjp_tape(const Tables* __restrict_
 // LDS of the forward and the adjoint rows, which take turns.
 constexpr size_t SPLIT_VJP_ROWS = sizeof(SplitRows) > sizeof(AdjRows) ? sizeof(SplitRows) : sizeof(AdjRows);
 
-// The adjoint of T consecutive steps from their tape on three wavefronts per
-// work item (one per block; see bx_split_adj.h).
-template <bool PAIRS, bool ONE_AXIS, int REGC>
-__global__ __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(PAIRS ? 1 : REGC > 2 ? 2 : 3))) void k_split_vjp_tape(
-    const Tables* __restrict__ tab, const WaveWork* __restrict__ work, int n_work, const int32_t* __restrict__ env_list,
-    const int32_t* __restrict__ type_off, int E, int Bm, int Am, const float* __restrict__ tape, size_t tstride, int T,
-    const float* __restrict__ act, Fields g_out, Fields g_in, float* __restrict__ g_act) {
-  extern __shared__ float4 split_lds_mem[];
-  const int w = xcd_block(blockIdx.x, gridDim.x);
-  if (w >= n_work) return;
-  const WaveWork wk = work[w];
-  AdjRows* L = reinterpret_cast<AdjRows*>(split_lds_mem);
-  PairLanes* pl = PAIRS ? reinterpret_cast<PairLanes*>(L + 1) : nullptr;
-  const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  auto rec_at = [&](int step, int sub) { return tape + step * tstride + ((size_t)sub * n_work + w) * TAPE_N * 64; };
-#define BX_ROLE(R, D)                                                                                              \
-  split_adj_run<R, D, PAIRS, REGC, true>(tab, wk, env_list, type_off, E, Bm, Am, act, g_out, g_in, g_act, T, rec_at, L, pl)
-  const bool one = ONE_AXIS || tab->type[wk.type].max_dof <= 1;
-  if (role == 0)
-    BX_ROLE(0, 1);
-  else if (role == 2)
-    BX_ROLE(2, 1);
-  else if (one)
-    BX_ROLE(1, 1);
-  else
-    BX_ROLE(1, 3);
-#undef BX_ROLE
-}
-
 // The adjoint of one step on three wavefronts per work item: the forward
 // substeps on two of them with their records in LDS, then the reverse ones.
 template <bool PAIRS, bool ONE_AXIS, int REGC>
@@ -688,7 +659,7 @@ __global__ __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(PAIRS ? 1 :
   block_exchange();
   auto rec_at = [&](int, int sub) { return tape + (size_t)sub * TAPE_N * 64; };
 #define BX_ROLE(R, D)                                                                                                \
-  split_adj_run<R, D, PAIRS, REGC, false>(tab, wk, env_list, type_off, E, Bm, Am, act, g_out, g_in, g_act, 1, rec_at, A, pl)
+  split_adj_run<R, D, PAIRS, REGC>(tab, wk, env_list, type_off, E, Bm, Am, act, g_out, g_in, g_act, 1, rec_at, A, pl)
   if (role == 0)
     BX_ROLE(0, 1);
   else if (role == 2)
@@ -708,13 +679,14 @@ bool any_pairs(const LaunchCtx& c) {
   return false;
 }
 
-// Whether the three-wavefront adjoints take a launch of n_work work items:
-// always without body-body contacts. Measured, 10 steps from their tape, one
-// wavefront per item against three (us): quadruped 1024 (147 items) 281 ->
-// 139, 4096 (586) 307 -> 195, 12288 (1756) 600 -> 387; biped 1024 296 -> 124,
-// 8192 (1639) 593 -> 365; chain 12288 313 -> 189. The body-body adjoint's
-// registers leave room for one block on a compute unit: grasp 2048 (228 items)
-// 493 -> 358, 3072 (342) 507 -> 687.
+// Whether the three-wavefront single-step adjoint takes a launch of n_work
+// work items: always without body-body contacts (one wavefront per item
+// against three, recomputing one step of 700 quadrupeds, 100 items: 42.2 ->
+// 24.2 us). The body-body adjoint's registers leave room for one block on a
+// compute unit (10 steps of grasp from a tape, the same reverse substeps: 228
+// items 493 -> 358 us, 342 items 507 -> 687). The adjoint from a tape stays on
+// one wavefront: over several steps the three-wavefront one's other rounding
+// is amplified, and a contact decided by a rounding may fall the other way.
 bool split_vjp_pays(const LaunchCtx& c, int n_work) { return !any_pairs(c) || n_work <= c.n_cu; }
 
 // Whether every type of the batch has joints of at most one axis: such
@@ -868,15 +840,13 @@ hipError_t launch_vjp_params(const LaunchCtx& c, const VjpSched& sched, Fields i
 hipError_t launch_vjp_tape(const LaunchCtx& c, const VjpSched& sched, const float* tape, size_t tstride, int T,
                            const float* act, Fields g_out, Fields g_in, float* g_act, hipStream_t s) {
   if (sched.n_work == 0 || T <= 0) return hipSuccess;
-  if (split_vjp_pays(c, sched.n_work)) {
-    const size_t lds = sizeof(AdjRows) + (any_pairs(c) ? sizeof(PairLanes) : 0);
-    LAUNCH_SPLIT(k_split_vjp_tape, lds, c.tab, sched.work, sched.n_work, c.env_list, c.type_off, c.E, c.Bm, c.Am, tape,
-                 tstride, T, act, g_out, g_in, g_act);
-  } else {
+  if (any_pairs(c))
     LAUNCH_AXES(k_fused_vjp_tape, true, dim3(sched.n_work), dim3(64), sizeof(XchRows) + sizeof(PairLanes), s, c.tab,
                 sched.work, sched.n_work, c.env_list, c.type_off, c.E, c.Bm, c.Am, tape, tstride, T, act, g_out, g_in,
                 g_act);
-  }
+  else
+    LAUNCH_AXES(k_fused_vjp_tape, false, dim3(sched.n_work), dim3(64), sizeof(XchRows), s, c.tab, sched.work,
+                sched.n_work, c.env_list, c.type_off, c.E, c.Bm, c.Am, tape, tstride, T, act, g_out, g_in, g_act);
   return hipGetLastError();
 }
 
