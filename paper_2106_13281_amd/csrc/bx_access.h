@@ -224,8 +224,11 @@ __device__ __forceinline__ void contact_add(float rho, const TypeT& ty, const Bo
   const bool on = in && num > 0.f;
   const float jn = num * __builtin_amdgcn_rcpf(kn);
   const float sp2 = fmaf(u.x, u.x, u.y * u.y);
-  const float isp = sp2 > 0.f ? __builtin_amdgcn_rsqf(sp2) : 0.f;  // no slip: t = 0 and jt = 0
-  const float tx = u.x * isp, ty_ = u.y * isp, sp = sp2 * isp;
+  // no friction where the slip is zero or NaN: t = 0 and jt = 0 by selects, as
+  // a product with NaN would carry it into the other components
+  const bool slip = sp2 > 0.f;
+  const float isp = __builtin_amdgcn_rsqf(sp2);
+  const float tx = slip ? u.x * isp : 0.f, ty_ = slip ? u.y * isp : 0.f, sp = slip ? sp2 * isp : 0.f;
   const v3 z = V(-(r.z * ty_), r.z * tx, fmaf(r.x, ty_, -(r.y * tx)));
   const v3 bz = mul(I, z);
   const float kt = B.inv_m + dot(z, bz);

@@ -261,10 +261,11 @@ __device__ __forceinline__ void contact_tan_fwd(const ContactT& c, bool has, con
   k.ikn = __builtin_amdgcn_rcpf(kn);
   k.jn = num * k.ikn;
   const float sp2 = fmaf(u.x, u.x, u.y * u.y);
-  k.isp = sp2 > 0.f ? __builtin_amdgcn_rsqf(sp2) : 0.f;  // no slip: t = 0, and with it every friction term
-  k.tx = u.x * k.isp;
-  k.ty = u.y * k.isp;
-  const float sp = sp2 * k.isp;
+  const bool slip = sp2 > 0.f;  // a zero or NaN slip: t = 0, and with it every friction term
+  k.isp = slip ? __builtin_amdgcn_rsqf(sp2) : 0.f;
+  k.tx = slip ? u.x * k.isp : 0.f;
+  k.ty = slip ? u.y * k.isp : 0.f;
+  const float sp = slip ? sp2 * k.isp : 0.f;
   const v3 zt = V(-(r.z * k.ty), r.z * k.tx, fmaf(r.x, k.ty, -(r.y * k.tx)));
   k.b = mul(I, zt);
   k.ikt = __builtin_amdgcn_rcpf(B.inv_m + dot(zt, k.b));

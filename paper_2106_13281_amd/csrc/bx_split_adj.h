@@ -48,7 +48,7 @@ struct AdjRows {
   float4 frame[64][7];    // 0 -> 1, 2: post-kinematic p, v, w, R and Iwinv (24 floats)
   float4 head[64][3];     // 0 -> 1, 2: cotangents of the force, torque, dv and dw sums
   float4 joint[65][5];    // 1 -> 0: the parent's cotangent (p, t, v, w), the child's (t, w); row 64 stays zero,
-                          // for lanes without an i-th child
+                          // for lanes without an i-th child or a joint
   float4 contact[64][3];  // 2 -> 0: cotangents of p, t, v, w
 };
 
@@ -124,6 +124,9 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
   int csrc[GATHER];  // the children's rows (the zero row where there is none)
 #pragma unroll
   for (int i = 0; i < GATHER; ++i) csrc[i] = i < B.nch ? base + (int)((B.ch_packed >> (4 * i)) & 15u) : 64;
+  // this body's joint row; a root has none (its lane's row holds the cotangents
+  // of no joint, NaN on a non-finite state)
+  const int jrow = has_joint ? lane : 64;
   if (JOINT && lane < 5) L->joint[64][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
 
   if (BODY) {
@@ -181,13 +184,13 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
           kn = advance(step - 1, S - 1);
         pin(kn.al);
         block_exchange();
-        const TBar c = tbar_get(L->contact[lane]), j = tbar_get(L->joint[lane]);
-        const float4 j3 = L->joint[lane][3];
-        const float2 j4 = *reinterpret_cast<const float2*>(&L->joint[lane][4]);
+        const TBar c = tbar_get(L->contact[lane]), j = tbar_get(L->joint[jrow]);
+        const float4 j3 = L->joint[jrow][3];
+        const float2 j4 = *reinterpret_cast<const float2*>(&L->joint[jrow][4]);
         TBar c0 = tbar_get(L->joint[csrc[0]]), c1 = tbar_get(L->joint[csrc[1]]);
         tbar_add(tot, c);
-        // this body's joint (a root's rows are zero): the child's p and v
-        // cotangents are the parent's negated
+        // this body's joint: the child's p and v cotangents are the parent's
+        // negated
         tot.p -= j.p;
         tot.v -= j.v;
         tot.t += V(j3.x, j3.y, j3.z);
@@ -255,14 +258,11 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
         const float4 h0 = L->head[lane][0], p0 = L->head[src_parent][0];
         const float2 h1 = *reinterpret_cast<const float2*>(&L->head[lane][1]);
         const float2 p1 = *reinterpret_cast<const float2*>(&L->head[src_parent][1]);
-        // a root has no joint: zero cotangents give zero results
-        const v3 z3 = V(0.f, 0.f, 0.f);
         TBar bP;
         v3 tC, wC;
         float ab[3];
-        joint_tan_back<MAXDOF>(J, k, sel(has_joint, V(h0.x, h0.y, h0.z), z3), sel(has_joint, V(h0.w, h1.x, h1.y), z3),
-                               sel(has_joint, V(p0.x, p0.y, p0.z), z3), sel(has_joint, V(p0.w, p1.x, p1.y), z3), bP, tC,
-                               wC, ab);
+        joint_tan_back<MAXDOF>(J, k, V(h0.x, h0.y, h0.z), V(h0.w, h1.x, h1.y), V(p0.x, p0.y, p0.z), V(p0.w, p1.x, p1.y),
+                               bP, tC, wC, ab);
         for (int x = 0; x < MAXDOF; ++x) ga[x] += ab[x];
         float4* r = L->joint[lane];
         tbar_put(r, bP);
