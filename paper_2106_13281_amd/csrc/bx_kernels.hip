@@ -483,8 +483,9 @@ __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const 
       // need none of it)
       v3 dv = V(0.f, 0.f, 0.f), dw = V(0.f, 0.f, 0.f);
       int cnt = 0;
-      ground_contacts<REGC, REGC == 2 && !TAPE && (!CL || PAIRS)>(&tab->contact[t][cfirst], Creg, n_con, max_con, ty, B, s,
-                                                                  f, dv, dw, cnt);
+      constexpr bool STRAIGHT = REGC == 2 && (!CL || PAIRS);
+      ground_contacts<REGC, STRAIGHT, STRAIGHT && !TAPE>(&tab->contact[t][cfirst], Creg, n_con, max_con, ty, B, s, f, dv, dw,
+                                                         cnt);
       // joint evaluated on every lane (a root uses its own state as the
       // parent and its result is discarded)
       JointOut jo = joint_eval<MAXDOF>(J, P, RP, s, jc, a);

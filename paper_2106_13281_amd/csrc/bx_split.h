@@ -12,17 +12,29 @@ namespace bx {
 // dynamic indexing; a slot no body of the type has is skipped by the whole
 // wave), the rest from the table C. Adds the velocity changes to dv, dw and
 // the applied candidates to cnt.
-// PEN_FIRST (two in registers): the penetrating candidates first, in
-// candidate order (the same sums), so that the second evaluation's impulse
-// runs only where a lane has two penetrating candidates, not wherever one has
-// its second (measured per kernel: biped 14.0 -> 13.0 ms, planar runner 10.3
-// -> 10.0, grasp 24.7 -> 24.2; the contact-lane kernels without body-body
-// contacts lost 2-3% and keep the plain order).
-template <int REGC, bool PEN_FIRST>
+// STRAIGHT: the impulses without branches (contact_add, the same sums), in
+// kernels that hold two candidates and no contact lanes, and in those with
+// body-body contacts (grasp 14040 environments x 20 steps, branches -> straight
+// with the penetrating first: 1199 -> 1172 us). With eight candidates or with contact lanes most slots
+// have a few lanes of one body in them, and the branches are the faster form:
+// manipulator x 20 steps, branches -> straight, one wavefront per item 12240
+// environments 341 -> 354 us, taped 18360 444 -> 530, two wavefronts 7674 303 ->
+// 315, taped 11511 397 -> 476.
+// PEN_FIRST (of STRAIGHT kernels): the penetrating candidates first, in
+// candidate order (the same sums), so that the second evaluation runs only
+// where a lane has two penetrating candidates, not wherever one has its second
+// (x 20 steps, without -> with: planar runner 2610 environments 149 -> 144 us,
+// biped 11700 519 -> 506, grasp 14040 1190 -> 1169, quadruped 2030 182 -> 178 but
+// 16380 370 -> 379).
+template <int REGC, bool STRAIGHT, bool PEN_FIRST>
 __device__ __forceinline__ void ground_contacts(const ContactT* __restrict__ C, const ContactT (&Creg)[REGC], int n_con,
                                                 int max_con, const TypeT& ty, const BodyT& B, const Body& s,
                                                 const Frame& f, v3& dv, v3& dw, int& cnt) {
-  if (PEN_FIRST) {
+  if (!STRAIGHT) {
+#pragma unroll
+    for (int k = 0; k < REGC; ++k)
+      if (k < max_con && n_con > k) cnt += contact_eval(Creg[k], ty, B, s, f, dv, dw) ? 1 : 0;
+  } else if (PEN_FIRST) {
     const v3 rl0 = mul(f.R, ld3(Creg[0].l)), rl1 = mul(f.R, ld3(Creg[REGC - 1].l));
     const float d0 = Creg[0].rho - (s.p.z + rl0.z), d1 = Creg[REGC - 1].rho - (s.p.z + rl1.z);
     const bool p0 = 0 < max_con && n_con > 0 && d0 > 0.f;
@@ -160,8 +172,8 @@ __device__ __forceinline__ void split_substep(const Tables* __restrict__ tab, in
       near0 = pair_near0(XC, *pl, ps0);
     }
     const Frame f = derive_inv(B, R);
-    ground_contacts<REGC, REGC == 2 && (!CL || PAIRS)>(&tab->contact[t][cfirst], Creg, n_con, max_con, ty, B, s, f, dv,
-                                                      dw, cnt);
+    constexpr bool STRAIGHT = REGC == 2 && (!CL || PAIRS);
+    ground_contacts<REGC, STRAIGHT, STRAIGHT>(&tab->contact[t][cfirst], Creg, n_con, max_con, ty, B, s, f, dv, dw, cnt);
     gyro = gyro_torque(B, s, f);
     if (groups) lane_group_sums(XC, lane, base, b, ty, B, dv, dw, cnt);
     if (PAIRS && ty.np > 0) pair_phase(tab, t, *pl, XC, lane, b, base, s, f, dv, dw, cnt, near0);
