@@ -554,14 +554,17 @@ __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const 
 // that path is compiled in (fewer registers). REGC: contact candidates per
 // body held in registers (8 for batches with a body of more than two, such
 // as a box's eight corners; 2 otherwise, where more registers only cost).
-// Three wavefronts per SIMD (168 registers, a few spilled) for one-axis
-// batches with two candidates: a batch too large for the split step is bound
-// by how many wavefronts hide one another's latency (quadruped x 20 steps, two
-// -> three per SIMD: 16384 environments 529 -> 413-417 us, 65536 1418 -> 1188-1224;
-// manipulator 65536 1837 -> 1551). With three-axis joints the spills cost more
-// (biped 16384 599 -> 728).
-template <bool ONE_AXIS, int REGC, bool CL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ONE_AXIS && REGC == REG_CONTACTS ? 3 : 2))) void k_fused(const Tables* __restrict__ tab, const WaveWork* __restrict__ work,
+// WPE: wavefronts per SIMD the registers are allotted for. Three (168
+// registers, 9 to 19 spilled) for one-axis batches with two candidates and more
+// than two work items per SIMD: such a launch is bound by how many wavefronts
+// hide one another's latency (x 20 steps, two -> three per SIMD: quadruped 17500
+// environments 485 -> 380 us, 28672 557 -> 523, manipulator 15000 610 -> 423). With
+// up to two items per SIMD the third place stays empty and the spills only cost
+// (one step, three -> two: quadruped 14280 25.5 -> 24.1 us, manipulator 12240 27.2 ->
+// 25.9; 20 steps even). With three-axis joints the spills cost more (biped x 20
+// steps 16384 599 -> 728).
+template <bool ONE_AXIS, int REGC, bool CL, int WPE = 2>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void k_fused(const Tables* __restrict__ tab, const WaveWork* __restrict__ work,
                                                int n_work, const int32_t* __restrict__ env_list,
                                                const int32_t* __restrict__ type_off, int E, int Bm, Fields in,
                                                Fields out, const float* __restrict__ acts, int Am, int T,
@@ -988,15 +991,20 @@ hipError_t launch_fused(const LaunchCtx& c, const WaveWork* work, int n_work, in
   else {
     const dim3 grid(cdiv(n_work, waves_per_block)), block(64 * waves_per_block);
     uint8_t* nf = flags ? c.nonfinite : nullptr;
-#define BX_FUSED(A, R, L)                                                                                         \
-  hipLaunchKernelGGL((k_fused<A, R, L>), grid, block, lds, s, c.tab, work, n_work, c.env_list, c.type_off, c.E, c.Bm, \
+    const bool three = n_work > 8 * c.n_cu;  // more than two work items per SIMD (see k_fused)
+#define BX_FUSED(A, R, ...)                                                                                       \
+  hipLaunchKernelGGL((k_fused<A, R, __VA_ARGS__>), grid, block, lds, s, c.tab, work, n_work, c.env_list, c.type_off, c.E, c.Bm, \
                      in, out, acts, c.Am, T, save_every, traj, nf, nullptr, 0)
-    if (one_axis && cl)
+    if (one_axis && cl && three)
+      BX_FUSED(true, REG_CONTACTS, true, 3);
+    else if (one_axis && cl)
       BX_FUSED(true, REG_CONTACTS, true);
     else if (cl)
       BX_FUSED(false, REG_CONTACTS, true);
     else if (one_axis && many_lane_contacts)
       BX_FUSED(true, 8, false);
+    else if (one_axis && three)
+      BX_FUSED(true, REG_CONTACTS, false, 3);
     else if (one_axis)
       BX_FUSED(true, REG_CONTACTS, false);
     else if (many_lane_contacts)
