@@ -338,7 +338,7 @@ __device__ __forceinline__ bool env_epilogue(const EnvArgs& ea, int t, const Typ
   // control cost: the squared actions as passed, summed over the
   // environment's lanes in body order
   float sq = 0.f;
-  for (int x = 0; x < MAXDOF; ++x) sq += raw[x] * raw[x];
+  for (int x = 0; x < MAXDOF; ++x) sq = fmaf(raw[x], raw[x], sq);
   float ctrl = 0.f;
   for (int i = 0; i < nb; ++i) ctrl += shfl(sq, base + i);
   if (live && b == P.root) {
