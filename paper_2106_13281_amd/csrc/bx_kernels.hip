@@ -829,17 +829,27 @@ __global__ void k_copy_state(int n3, int n4, Fields in, Fields out) {
 static inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
 // ------------------------------------------------------------------ environment layer
-// Whether the two-wavefront kernels take a launch of n_work work items: up to
-// five per compute unit (1280 on 256), where both wavefronts of every item
-// are resident and the SIMDs have issue slots to spare. Measured, 20 steps,
-// one wavefront per item against two (us, two runs of each): quadruped 1024
-// (147 items) 234-235 -> 180-182, 4096 (586) 261 -> 201-203, 8192 (1171)
-// 287-294 -> 288-292, 8960 (1280) 293-298 -> 288-293; biped 2048 (410) 263-267
-// -> 218, 6400 (1280) 307 -> 297-309: even at the line, and past it more work
-// items than fit queue up. With body-body
-// contacts a block's LDS (42 KB) lets a compute unit hold three: grasp 4096
-// (683) 548-554 -> 508, 4608 (768) 505-508 -> 460, 6144 (1024) 541 -> 771.
-static bool split_pays(const LaunchCtx& c, int n_work, bool pairs) { return n_work <= (pairs ? 3 : 5) * c.n_cu; }
+// Whether the two-wavefront kernels take a launch of n_work work items over T
+// steps. Up to four per compute unit, two wavefronts per SIMD, they win
+// throughout; a fifth puts a third wavefront on SIMDs, and both wavefronts of
+// an item load its tables and states, which few steps do not repay; past five
+// a third wavefront on most SIMDs makes the late ones longer. Measured, one
+// wavefront per item -> two (us):
+//   4 per compute unit: one step of quadruped 18.8 -> 18.4, biped 20.0 -> 18.7,
+//     environment step 19.9 -> 19.9, 21.7 -> 20.9; 20 steps 246 -> 212, 256 -> 223
+//   5: one step of quadruped 20.4 -> 21.3, manipulator 23.9 -> 24.4, mixed 25.7 -> 27.1,
+//     environment step 22.2 -> 22.7, 25.4 -> 26.1, 27.8 -> 28.8; 2 steps of quadruped
+//     37.3 -> 38.1; 4 steps 65.5 -> 65.4, 76.0 -> 73.2, 75.8 -> 75.8; 20 steps 275 -> 272,
+//     328 -> 312, 309 -> 297; taped, one step 27.1 -> 27.9, 26.9 -> 27.5, 30.2 -> 30.8, 2
+//     steps 42.5 -> 42.9, 51.0 -> 50.2, 48.7 -> 46.5, 20 steps 316 -> 311, 430 -> 409,
+//     385 -> 349
+//   5.5: 20 steps of chain 274 -> 298, quadruped 277 -> 311
+// With body-body contacts a block's LDS (42 KB) lets a compute unit hold three:
+// grasp at 3 per compute unit one step 61.6 -> 60.2, 20 steps 856 -> 821; past it
+// blocks queue up, at 3.05 61.7 -> 66.6, 731 -> 839.
+static bool split_pays(const LaunchCtx& c, int n_work, bool pairs, int T, bool tape) {
+  return n_work <= (pairs ? 3 : T < (tape ? 2 : 4) ? 4 : 5) * c.n_cu;
+}
 
 hipError_t launch_env_step(const LaunchCtx& c, const WaveWork* work, int n_work, int waves_per_block,
                            const EnvT* env, int Omax, Fields in, Fields out, const float* act, Fields reset, float* obs,
@@ -858,7 +868,7 @@ hipError_t launch_env_step(const LaunchCtx& c, const WaveWork* work, int n_work,
 #define BX_ENV(P, R, L)                                                                                            \
   hipLaunchKernelGGL((k_fused_env<P, R, L>), grid, block, lds, s, c.tab, work, n_work, c.env_list, c.type_off, c.E, \
                      c.Bm, in, out, act, c.Am, nf, ea)
-  if (split_pays(c, n_work, pairs) && (cl || !many_contacts)) {
+  if (split_pays(c, n_work, pairs, 1, false) && (cl || !many_contacts)) {
     const dim3 sgrid(n_work), sblock(128);
     const Fields none{nullptr, nullptr, nullptr, nullptr};
 #define BX_SPLIT(P, L)                                                                                             \
@@ -923,7 +933,7 @@ hipError_t launch_fused(const LaunchCtx& c, const WaveWork* work, int n_work, in
   // (further ones, of a type whose lanes did not fit, are read from the table)
   if (cl) many_lane_contacts = false;
   const size_t lds = fused_lds_per_wave(pairs) * waves_per_block;
-  if (split_pays(c, n_work, pairs) && (tape || !many_lane_contacts)) {
+  if (split_pays(c, n_work, pairs, T, tape != nullptr) && (tape || !many_lane_contacts)) {
     const dim3 grid(n_work), block(128);
     uint8_t* nf = flags ? c.nonfinite : nullptr;
     const EnvArgs none{};

@@ -36,3 +36,36 @@ def test_control_cost_rounding(E):
                 sq = (r * r + sq).astype(np.float32)
         ctrl += sq
     assert np.array_equal(reward.cpu().numpy(), -ctrl)
+
+
+@pytest.mark.parametrize("name,per_wave", SYSTEMS)
+def test_few_steps_around_the_line(name, per_wave):
+    """Steps, environment steps and short rollouts take two wavefronts up to four work
+    items per compute unit (three with body-body contacts), rollouts of four steps up
+    to five: the last batch on two against the first environments of the next, and
+    between the lines a short rollout against the first steps of a longer one (zero
+    tolerance)."""
+    E = (3 if name == "grasp" else 4) * n_cu() * per_wave
+    big = braxmi.System(synth.system_text(name), E + 1, device=0)
+    small = braxmi.System(synth.system_text(name), E, device=0)
+    s, acts = inputs(big, 6, 4)
+    x, a = head(s, E), acts[..., :E].contiguous()
+    for T in (1, 3):
+        out, _ = big.rollout(s, acts[:T].contiguous(), flags=braxmi.BRAX_NONFINITE_FLAGS)
+        so, _ = small.rollout(x, a[:T].contiguous(), flags=braxmi.BRAX_NONFINITE_FLAGS)
+        assert equal(so.fields(), head(out, E).fields()) and torch.equal(small.nonfinite(), big.nonfinite()[:E])
+    _, traj = big.rollout(s, acts, save_every=1)        # four steps: two wavefronts
+    assert equal(out.fields(), [f[2] for f in traj.fields()])
+    for y in (big, small):
+        y.env_configure([dict(z_min=0.15, z_max=0.6)])
+    reset = big.default_qp()
+    eo, obs, rew, done = big.env_step(s, acts[0].contiguous(), reset)
+    so, o, r, d = small.env_step(x, a[0].contiguous(), head(reset, E))
+    assert equal(so.fields(), head(eo, E).fields()) and torch.equal(d, done[:E])
+    assert torch.equal(o, obs[:, :E]) and torch.equal(r, rew[:E])
+    _, tape1 = big.rollout_tape(s, acts[:1].contiguous())   # taped: one wavefront for one step, two for more
+    _, tape2 = big.rollout_tape(s, acts[:2].contiguous())
+    g = head(s, E + 1)
+    for f, h in zip(big.step_vjp_tape(tape1[0], acts[0].contiguous(), g)[0].fields(),
+                    big.step_vjp_tape(tape2[0], acts[0].contiguous(), g)[0].fields()):
+        assert torch.equal(f, h)
