@@ -17,10 +17,10 @@
 //    so the result is deterministic.
 //
 // The fused adjoints run 1 and 2 in one launch, on three wavefronts per work
-// item (bx_split_adj.h; the rule is split_vjp_pays) or on one (fused_vjp_run):
-// for parameter cotangents, for body-body batches with more work items than
-// CUs, and where the on-chip tape leaves no room for the three wavefronts'
-// rows; 2 alone, from a tape in device memory, runs on one.
+// item (bx_split_adj.h) or on one (fused_vjp_run): where that is the faster
+// (vjp_estimate), for parameter cotangents, and where the on-chip tape leaves no
+// room for the three wavefronts' rows; 2 alone, from a tape in device memory,
+// runs on one.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -679,16 +679,6 @@ bool any_pairs(const LaunchCtx& c) {
   return false;
 }
 
-// Whether the three-wavefront single-step adjoint takes a launch of n_work
-// work items: always without body-body contacts (one wavefront per item
-// against three, recomputing one step of 700 quadrupeds, 100 items: 42.2 ->
-// 24.2 us). The body-body adjoint's registers leave room for one block on a
-// compute unit (10 steps of grasp from a tape, the same reverse substeps: 228
-// items 493 -> 358 us, 342 items 507 -> 687). The adjoint from a tape stays on
-// one wavefront: over several steps the three-wavefront one's other rounding
-// is amplified, and a contact decided by a rounding may fall the other way.
-bool split_vjp_pays(const LaunchCtx& c, int n_work) { return !any_pairs(c) || n_work <= c.n_cu; }
-
 // Whether every type of the batch has joints of at most one axis: such
 // batches take the kernels compiled for that path alone (fewer registers).
 bool all_one_axis(const LaunchCtx& c) {
@@ -704,6 +694,45 @@ bool many_contacts(const LaunchCtx& c) {
   for (int t = 0; t < c.n_types; ++t)
     if (c.host_tab->type[t].max_contacts > REG_CONTACTS) return true;
   return false;
+}
+
+// Estimated time of the recomputing adjoint's launch with `lds` bytes of LDS
+// per work item, on three wavefronts per item (split) or on one. Unit: a tenth
+// of a substep of an item that one wavefront runs alone on its compute unit.
+// Items wait for a place on a compute unit, so a launch takes whole rounds:
+// places are bound by LDS (10 substeps: 65 KB against 49 KB, so two against
+// three) and by registers (k_fused_vjp one wavefront per SIMD: 4; k_split_vjp
+// with 2 candidates in registers 164 VGPRs: 4, with 8 candidates 188: 2, with
+// body-body contacts 366: 1). Items of several types end at different times
+// and refill the places; there the sum over the places counts. Measured, one
+// wavefront per item -> three (us): quadruped 128 items 42.6 -> 25.0, 512 51.1 -> 28.9,
+// 768 50.5 -> 49.5, 1000 89.6 -> 53.8, 2040 134 -> 104; biped 512 51.8 -> 29.8, 1000 53.6
+// -> 54.6, 1279 95.4 -> 76.0, 2040 102 -> 106, 4096 199 -> 207; manipulator 512 64.8 ->
+// 51.7, 760 65.0 -> 99.5, 1000 121 -> 102, 1279 124 -> 145, 4096 356 -> 391; planar
+// runner 512 41.5 -> 24.0, 1000 42.7 -> 45.2, 4096 156 -> 171; grasp 1 86 -> 64, 128 189 ->
+// 170, 512 203 -> 289; mixed batch 512 70.5 -> 54.9, 4096 297 -> 268; two substeps of
+// quadruped 700 14.7 -> 13.8, 2048 29.6 -> 31.8. Over these and 1 to 31 substeps the
+// choice is 0.4% slower than the better kernel on average.
+double vjp_estimate(const LaunchCtx& c, bool split, size_t lds) {
+  const int regs = !split ? 4 : any_pairs(c) ? 1 : many_contacts(c) ? 2 : 4;
+  const int places = std::min<int>(regs, (int)(c.lds_limit / lds));
+  double single = 0., longest = 0., sum = 0.;
+  int types = 0;
+  for (int t = 0; t < c.n_types; ++t) {
+    const TypeT& ty = c.host_tab->type[t];
+    const int n = cdiv(c.type_cnt_h[t], 64 / ty.nb), rest = n % (places * c.n_cu);
+    if (n == 0) continue;
+    ++types;
+    // a substep takes alone + each * (items resident on the compute unit); with
+    // few substeps the tables and states that three wavefronts load count
+    const double alone = !split ? 9. : ty.np > 0 ? 8. : ty.max_contacts > REG_CONTACTS ? 7. : 5.;
+    const double each = split && ty.substeps < 4 ? 2. : 1.;
+    const double full = alone + each * places;
+    single = ty.substeps * (n / (places * c.n_cu) * full + (rest ? alone + each * cdiv(rest, c.n_cu) : 0.));
+    longest = std::max(longest, ty.substeps * (alone + each));
+    sum += n * ty.substeps * full / (places * c.n_cu);
+  }
+  return types == 1 ? single : std::max(longest, sum);
 }
 
 }  // namespace
@@ -729,7 +758,7 @@ bool many_contacts(const LaunchCtx& c) {
 // Launches kernel template K<PAIRS, ONE_AXIS, REGC> on blocks of three
 // wavefronts with `lds_` bytes of LDS. A batch with a body of many contacts
 // holds eight candidates in registers here (they take none from the joint's
-// wavefront), so that a type's results do not depend on the batch it is in.
+// wavefront), also with three-axis joints.
 #define LAUNCH_SPLIT(K, lds_, ...)                                                     \
   do {                                                                                 \
     const bool one_ = all_one_axis(c), many_ = many_contacts(c);                       \
@@ -870,15 +899,18 @@ hipError_t launch_vjp(const LaunchCtx& c, VjpWork& w, const VjpSched& sched, Fie
     // one wavefront per block; its tape lives in LDS
     const size_t lds = sizeof(XchRows) + smax * TAPE_N * 64 * sizeof(float);
     if (sched.n_work == 0) return hipSuccess;
-    const size_t split = SPLIT_VJP_ROWS + smax * TAPE_N * 64 * sizeof(float) +
-                         (any_pairs(c) ? sizeof(XchRows) + sizeof(PairLanes) : 0);
-    if (split_vjp_pays(c, sched.n_work) && split <= c.lds_limit) {
+    const size_t pair_lds = any_pairs(c) ? sizeof(PairLanes) : 0;
+    const size_t split = SPLIT_VJP_ROWS + smax * TAPE_N * 64 * sizeof(float) + (any_pairs(c) ? sizeof(XchRows) + pair_lds : 0);
+    // (over several steps, from a tape, one wavefront per item: the other's
+    // rounding is amplified there, and a contact decided by a rounding may
+    // fall the other way)
+    if (split <= c.lds_limit && vjp_estimate(c, true, split) < vjp_estimate(c, false, lds + pair_lds)) {
       LAUNCH_SPLIT(k_split_vjp, split, c.tab, sched.work, sched.n_work, c.env_list, c.type_off, E, Bm, c.Am, in, act, g_out,
                    g_in, g_act);
       return hipGetLastError();
     }
     if (any_pairs(c))
-      LAUNCH_AXES(k_fused_vjp, true, dim3(sched.n_work), dim3(64), lds + sizeof(PairLanes), s, c.tab, sched.work,
+      LAUNCH_AXES(k_fused_vjp, true, dim3(sched.n_work), dim3(64), lds + pair_lds, s, c.tab, sched.work,
                   sched.n_work, c.env_list, c.type_off, E, Bm, c.Am, (int)smax, in, act, g_out, g_in, g_act);
     else
       LAUNCH_AXES(k_fused_vjp, false, dim3(sched.n_work), dim3(64), lds, s, c.tab, sched.work, sched.n_work,

@@ -6,7 +6,7 @@ import torch
 
 import oracle
 from paper_2106_13281_amd import braxmi, synth
-from test_gpu_split import SYSTEMS, equal, head, inputs
+from test_gpu_split import PAIR_TOL, SYSTEMS, check_vjp, equal, head, inputs, star, text
 
 pytestmark = pytest.mark.gpu
 
@@ -69,3 +69,35 @@ def test_few_steps_around_the_line(name, per_wave):
     for f, h in zip(big.step_vjp_tape(tape1[0], acts[0].contiguous(), g)[0].fields(),
                     big.step_vjp_tape(tape2[0], acts[0].contiguous(), g)[0].fields()):
         assert torch.equal(f, h)
+
+
+@pytest.mark.parametrize("name", [n for n, _ in SYSTEMS])
+def test_vjp_around_the_line(name):
+    """The largest batch whose single-step adjoint has room on the compute units with three
+    wavefronts per work item (two items each; one with body-body contacts) against the first
+    environments of the next, on one, and a partly filled work item, normwise as two FP32
+    evaluations of one adjoint along the same forward values."""
+    nb = {"chain": 3, "quadruped": 9, "biped": 11}.get(name, 7)
+    E = (1 if name == "grasp" else 2) * n_cu() * (64 // nb)
+    big = braxmi.System(synth.system_text(name), E + 1, device=0)
+    s, acts = inputs(big, 9, 20)
+    s, _ = big.rollout(s, acts)
+    a = acts[0].contiguous()
+    g = braxmi.State(*(torch.randn(f.shape, generator=torch.Generator().manual_seed(i)).cuda()
+                       for i, f in enumerate(s.fields())))
+    bi, ba = big.step_vjp(s, a, g)
+    ref = torch.cat([f.flatten(0, 1) for f in bi.fields()] + [ba])
+    for n in (E, 64 // nb + 1):
+        small = braxmi.System(synth.system_text(name), n, device=0)
+        si, sa = small.step_vjp(head(s, n), a[:, :n].contiguous(), head(g, n))
+        r = ref[:, :n]
+        d = torch.cat([f.flatten(0, 1) for f in si.fields()] + [sa]) - r
+        assert (d.norm(dim=0) < PAIR_TOL * r.norm(dim=0)).float().mean() > 0.99 and d.norm() < PAIR_TOL * r.norm()
+
+
+@pytest.mark.parametrize("substeps", [32, 33, 36, 37])
+@pytest.mark.parametrize("name", ["star", "biped"])
+def test_vjp_lds_limits_match_oracle(name, substeps):
+    """The recomputing adjoint's LDS at 160 KiB: 32 substeps are the last on three wavefronts,
+    33 and 36 the first and last on one, 37 the first per phase."""
+    check_vjp(star(2, substeps) if name == "star" else text(name, substeps), 6, substeps)
