@@ -72,15 +72,15 @@ __device__ __forceinline__ void pin(JointTan<MAXDOF>& k) {
     pin(k.n1);
   }
 }
-// The reverse substeps of T steps on one of the three wavefronts (ROLE 0:
-// body, 1: joint, 2: contact). rec_at(step, sub): the tape record of a substep.
-// act, g_act [T][Am][E].
-template <int ROLE, int MAXDOF, bool PAIRS, int REGC, class Rec>
+// The reverse substeps of one step on one of the three wavefronts (ROLE 0:
+// body, 1: joint, 2: contact), from their tape records in LDS. act, g_act
+// [Am][E].
+template <int ROLE, int MAXDOF, bool PAIRS, int REGC>
 __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, const WaveWork& wk,
                                               const int32_t* __restrict__ env_list,
                                               const int32_t* __restrict__ type_off, int E, int Bm, int Am,
                                               const float* __restrict__ act, const Fields& g_out, const Fields& g_in,
-                                              float* __restrict__ g_act, int T, const Rec& rec_at, AdjRows* L,
+                                              float* __restrict__ g_act, const float* tape, AdjRows* L,
                                               PairLanes* pl) {
   constexpr bool BODY = ROLE == 0, JOINT = ROLE == 1, CONTACT = ROLE == 2;
   const int t = wk.type;
@@ -131,18 +131,15 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
 
   if (BODY) {
     TapeRec rec;
-    auto fetch = [&](int step, int sub) { wtape_fetch<false>(rec_at(step, sub), lane, rec); };
+    auto fetch = [&](int sub) { wtape_fetch<false>(tape + (size_t)sub * TAPE_N * 64, lane, rec); };
     // the substep in rec: what this wavefront needs of it, and the frame row
     // of the others; then the record of the substep before it
-    auto advance = [&](int step, int sub) {
+    auto advance = [&](int sub) {
       Body post;
       v3 ttot;
       int n;
       wtape_unpack(rec, post, ttot, n);
-      if (sub > 0)
-        fetch(step, sub - 1);
-      else if (step > 0)
-        fetch(step - 1, S - 1);
+      if (sub > 0) fetch(sub - 1);
       const q4 q0 = post.q;
       kinematic(B, post, h);
       const BodyTan k = body_tan(B, q0, post, ttot, n, h);
@@ -155,8 +152,8 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
       r[5] = make_float4(k.Iwinv.zz, k.Iwinv.xy, k.Iwinv.xz, k.Iwinv.yz);
       return k;
     };
-    fetch(T - 1, S - 1);
-    BodyTan k = advance(T - 1, S - 1);
+    fetch(S - 1);
+    BodyTan k = advance(S - 1);
     TBar G = tbar_zero();
     if (live) {
       const Bar g = load_bar(g_out, b, e, Bm, E);
@@ -164,56 +161,46 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
     }
     q4 gq = q4{0.f, 0.f, 0.f, 0.f};
     block_exchange();
-    for (int step = T - 1; step >= 0; --step) {
-      for (int sub = S - 1; sub >= 0; --sub) {
-        v3 fb, tb, dvb, dwb;
-        body_head(B, k, h, G, fb, tb, dvb, dwb);
-        L->head[lane][0] = make_float4(fb.x, fb.y, fb.z, tb.x);
-        L->head[lane][1] = make_float4(tb.y, tb.z, dvb.x, dvb.y);
-        L->head[lane][2] = make_float4(dvb.z, dwb.x, dwb.y, dwb.z);
-        block_exchange();
-        TBar tot = G;
-        potential_tan(B, k, h, G.w, tb, tot);
-        pin(tot.t);
-        pin(tot.w);
-        // the next substep's frame while the other wavefronts are busy
-        BodyTan kn = k;
-        if (sub > 0)
-          kn = advance(step, sub - 1);
-        else if (step > 0)
-          kn = advance(step - 1, S - 1);
-        pin(kn.al);
-        block_exchange();
-        const TBar c = tbar_get(L->contact[lane]), j = tbar_get(L->joint[jrow]);
-        const float4 j3 = L->joint[jrow][3];
-        const float2 j4 = *reinterpret_cast<const float2*>(&L->joint[jrow][4]);
-        TBar c0 = tbar_get(L->joint[csrc[0]]), c1 = tbar_get(L->joint[csrc[1]]);
-        tbar_add(tot, c);
-        // this body's joint: the child's p and v cotangents are the parent's
-        // negated
-        tot.p -= j.p;
-        tot.v -= j.v;
-        tot.t += V(j3.x, j3.y, j3.z);
-        tot.w += V(j3.w, j4.x, j4.y);
+    for (int sub = S - 1; sub >= 0; --sub) {
+      v3 fb, tb, dvb, dwb;
+      body_head(B, k, h, G, fb, tb, dvb, dwb);
+      L->head[lane][0] = make_float4(fb.x, fb.y, fb.z, tb.x);
+      L->head[lane][1] = make_float4(tb.y, tb.z, dvb.x, dvb.y);
+      L->head[lane][2] = make_float4(dvb.z, dwb.x, dwb.y, dwb.z);
+      block_exchange();
+      TBar tot = G;
+      potential_tan(B, k, h, G.w, tb, tot);
+      pin(tot.t);
+      pin(tot.w);
+      // the next substep's frame while the other wavefronts are busy
+      BodyTan kn = k;
+      if (sub > 0) kn = advance(sub - 1);
+      pin(kn.al);
+      block_exchange();
+      const TBar c = tbar_get(L->contact[lane]), j = tbar_get(L->joint[jrow]);
+      const float4 j3 = L->joint[jrow][3];
+      const float2 j4 = *reinterpret_cast<const float2*>(&L->joint[jrow][4]);
+      TBar c0 = tbar_get(L->joint[csrc[0]]), c1 = tbar_get(L->joint[csrc[1]]);
+      tbar_add(tot, c);
+      // this body's joint: the child's p and v cotangents are the parent's
+      // negated
+      tot.p -= j.p;
+      tot.v -= j.v;
+      tot.t += V(j3.x, j3.y, j3.z);
+      tot.w += V(j3.w, j4.x, j4.y);
+      tbar_add(tot, c0);
+      tbar_add(tot, c1);
+      if (ty.max_children > 2) {
+        c0 = tbar_get(L->joint[csrc[2]]);
+        c1 = tbar_get(L->joint[csrc[3]]);
         tbar_add(tot, c0);
         tbar_add(tot, c1);
-        if (ty.max_children > 2) {
-          c0 = tbar_get(L->joint[csrc[2]]);
-          c1 = tbar_get(L->joint[csrc[3]]);
-          tbar_add(tot, c0);
-          tbar_add(tot, c1);
-        }
-        for (int i = GATHER; i < ty.max_children; ++i)
-          tbar_add(tot, tbar_get(L->joint[i < B.nch ? base + (int)((B.ch_packed >> (4 * i)) & 15u) : 64]));
-        G = kinematic_tan(B, ty.frozen, k, h, tot);
-        if (sub == 0) {
-          // a step hands on a quaternion cotangent, as steps differentiated
-          // one by one do
-          gq = kinematic_tan_quat(k, h, tot.t);
-          G.t = quat_tan(kn.q1, gq);
-        }
-        k = kn;
       }
+      for (int i = GATHER; i < ty.max_children; ++i)
+        tbar_add(tot, tbar_get(L->joint[i < B.nch ? base + (int)((B.ch_packed >> (4 * i)) & 15u) : 64]));
+      G = kinematic_tan(B, ty.frozen, k, h, tot);
+      if (sub == 0) gq = kinematic_tan_quat(k, h, tot.t);
+      k = kn;
     }
     if (live) {
       store_bar(g_in, Bar{G.p, gq, G.v, G.w}, b, e, Bm, E);
@@ -222,12 +209,10 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
     return;
   }
 
-  // actions of the step being differentiated (the last one first)
-  const size_t AE = (size_t)Am * E;
-  float a[3] = {0.f, 0.f, 0.f}, raw[3] = {0.f, 0.f, 0.f};
+  float a[3] = {0.f, 0.f, 0.f}, raw[3] = {0.f, 0.f, 0.f}, ga[3] = {0.f, 0.f, 0.f};
   if (JOINT && has_joint)
     for (int x = 0; x < MAXDOF; ++x) {
-      raw[x] = act_raw(act + (T - 1) * AE, J, x, e, E);
+      raw[x] = act_raw(act, J, x, e, E);
       a[x] = clampf(raw[x], J.act_lo[x], J.act_hi[x]);
     }
   auto frame_get = [&](int src, Body& post, m3& R) {
@@ -240,82 +225,69 @@ __device__ __forceinline__ void split_adj_run(const Tables* __restrict__ tab, co
     return r4;
   };
   block_exchange();
-  for (int step = T - 1; step >= 0; --step) {
-    float raw_prev[3] = {0.f, 0.f, 0.f}, ga[3] = {0.f, 0.f, 0.f};
-    if (JOINT && has_joint && step > 0)
-      for (int x = 0; x < MAXDOF; ++x) raw_prev[x] = act_raw(act + (step - 1) * AE, J, x, e, E);
-    for (int sub = S - 1; sub >= 0; --sub) {
-      Body post;
-      if (JOINT) {
-        Body P;
-        m3 R, RP;
-        (void)frame_get(lane, post, R);
-        (void)frame_get(src_parent, P, RP);
-        JointTan<MAXDOF> k;
-        joint_tan_fwd<MAXDOF>(J, P, RP, post, R, a, k);
-        pin(k);
-        block_exchange();
-        const float4 h0 = L->head[lane][0], p0 = L->head[src_parent][0];
-        const float2 h1 = *reinterpret_cast<const float2*>(&L->head[lane][1]);
-        const float2 p1 = *reinterpret_cast<const float2*>(&L->head[src_parent][1]);
-        TBar bP;
-        v3 tC, wC;
-        float ab[3];
-        joint_tan_back<MAXDOF>(J, k, V(h0.x, h0.y, h0.z), V(h0.w, h1.x, h1.y), V(p0.x, p0.y, p0.z), V(p0.w, p1.x, p1.y),
-                               bP, tC, wC, ab);
-        for (int x = 0; x < MAXDOF; ++x) ga[x] += ab[x];
-        float4* r = L->joint[lane];
-        tbar_put(r, bP);
-        r[3] = make_float4(tC.x, tC.y, tC.z, wC.x);
-        *reinterpret_cast<float2*>(&r[4]) = make_float2(wC.y, wC.z);
-      } else {
-        Frame f;
-        const float4 r4 = frame_get(lane, post, f.R), r5 = L->frame[lane][5];
-        f.Iwinv = s3{r4.z, r4.w, r5.x, r5.y, r5.z, r5.w};
-        f.Iw = s3_zero();
-        ContactTan k[2];
-        const bool any0 = 0 < ty.max_contacts, any1 = 1 < ty.max_contacts;
-        if (any0) contact_tan_fwd(Creg[0], n_con > 0, ty, B, post, f.R, f.Iwinv, k[0]);
-        if (any1) contact_tan_fwd(Creg[REGC > 1 ? 1 : 0], n_con > 1, ty, B, post, f.R, f.Iwinv, k[1]);
-        block_exchange();
-        const float4 h1 = L->head[lane][1], h2 = L->head[lane][2];
-        const v3 dvb = V(h1.z, h1.w, h2.x), dwb = V(h2.y, h2.z, h2.w);
-        const ContactBar cb = contact_bar(B, f.Iwinv, dvb, dwb);
-        TBar r = tbar_zero();
-        if (any0 && k[0].on) contact_tan_back(k[0], ty, post.w, cb, r);
-        if (any1 && k[1].on) contact_tan_back(k[1], ty, post.w, cb, r);
-#pragma unroll
-        for (int i = 2; i < REGC; ++i)
-          if (i < ty.max_contacts && n_con > i) contact_tan(Creg[i], ty, B, post, f, cb, r);
-        for (int i = REGC; i < n_con; ++i) contact_tan(tab->contact[t][B.c0 + i], ty, B, post, f, cb, r);
-        if (PAIRS && ty.np > 0) {
-          Bar pb = bar_zero();
-          FrameBar fr = framebar_zero();
-          float invm_bar = 0.f, mu_bar = 0.f;  // not kept
-          pair_phase_adj(tab, t, *pl, b, base, post, f, dvb, dwb, pb, fr, invm_bar, mu_bar);
-          tbar_add(r, TBar{pb.p, frame_tan(B, f, fr), pb.v, pb.w});
-        }
-        tbar_put(L->contact[lane], r);
-      }
-      block_exchange();
-    }
+  for (int sub = S - 1; sub >= 0; --sub) {
+    Body post;
     if (JOINT) {
-      // this step's action cotangents (zero where the action was clamped)
-      if (live) {
-        float* ga_t = g_act + step * AE;
-        if (has_joint)
-          for (int x = 0; x < MAXDOF; ++x)
-            if (x < J.dof && J.act[x] >= 0)
-              ga_t[(size_t)J.act[x] * E + e] = (raw[x] >= J.act_lo[x] && raw[x] <= J.act_hi[x]) ? ga[x] : 0.f;
-        if (b == 0)
-          for (int x = ty.na; x < Am; ++x) ga_t[(size_t)x * E + e] = 0.f;
+      Body P;
+      m3 R, RP;
+      (void)frame_get(lane, post, R);
+      (void)frame_get(src_parent, P, RP);
+      JointTan<MAXDOF> k;
+      joint_tan_fwd<MAXDOF>(J, P, RP, post, R, a, k);
+      pin(k);
+      block_exchange();
+      const float4 h0 = L->head[lane][0], p0 = L->head[src_parent][0];
+      const float2 h1 = *reinterpret_cast<const float2*>(&L->head[lane][1]);
+      const float2 p1 = *reinterpret_cast<const float2*>(&L->head[src_parent][1]);
+      TBar bP;
+      v3 tC, wC;
+      float ab[3];
+      joint_tan_back<MAXDOF>(J, k, V(h0.x, h0.y, h0.z), V(h0.w, h1.x, h1.y), V(p0.x, p0.y, p0.z), V(p0.w, p1.x, p1.y),
+                             bP, tC, wC, ab);
+      for (int x = 0; x < MAXDOF; ++x) ga[x] += ab[x];
+      float4* r = L->joint[lane];
+      tbar_put(r, bP);
+      r[3] = make_float4(tC.x, tC.y, tC.z, wC.x);
+      *reinterpret_cast<float2*>(&r[4]) = make_float2(wC.y, wC.z);
+    } else {
+      Frame f;
+      const float4 r4 = frame_get(lane, post, f.R), r5 = L->frame[lane][5];
+      f.Iwinv = s3{r4.z, r4.w, r5.x, r5.y, r5.z, r5.w};
+      f.Iw = s3_zero();
+      ContactTan k[2];
+      const bool any0 = 0 < ty.max_contacts, any1 = 1 < ty.max_contacts;
+      if (any0) contact_tan_fwd(Creg[0], n_con > 0, ty, B, post, f.R, f.Iwinv, k[0]);
+      if (any1) contact_tan_fwd(Creg[REGC > 1 ? 1 : 0], n_con > 1, ty, B, post, f.R, f.Iwinv, k[1]);
+      block_exchange();
+      const float4 h1 = L->head[lane][1], h2 = L->head[lane][2];
+      const v3 dvb = V(h1.z, h1.w, h2.x), dwb = V(h2.y, h2.z, h2.w);
+      const ContactBar cb = contact_bar(B, f.Iwinv, dvb, dwb);
+      TBar r = tbar_zero();
+      if (any0 && k[0].on) contact_tan_back(k[0], ty, post.w, cb, r);
+      if (any1 && k[1].on) contact_tan_back(k[1], ty, post.w, cb, r);
+#pragma unroll
+      for (int i = 2; i < REGC; ++i)
+        if (i < ty.max_contacts && n_con > i) contact_tan(Creg[i], ty, B, post, f, cb, r);
+      for (int i = REGC; i < n_con; ++i) contact_tan(tab->contact[t][B.c0 + i], ty, B, post, f, cb, r);
+      if (PAIRS && ty.np > 0) {
+        Bar pb = bar_zero();
+        FrameBar fr = framebar_zero();
+        float invm_bar = 0.f, mu_bar = 0.f;  // not kept
+        pair_phase_adj(tab, t, *pl, b, base, post, f, dvb, dwb, pb, fr, invm_bar, mu_bar);
+        tbar_add(r, TBar{pb.p, frame_tan(B, f, fr), pb.v, pb.w});
       }
-      if (has_joint)
-        for (int x = 0; x < MAXDOF; ++x) {
-          raw[x] = raw_prev[x];
-          a[x] = clampf(raw[x], J.act_lo[x], J.act_hi[x]);
-        }
+      tbar_put(L->contact[lane], r);
     }
+    block_exchange();
+  }
+  if (JOINT && live) {
+    // action cotangents (zero where the action was clamped)
+    if (has_joint)
+      for (int x = 0; x < MAXDOF; ++x)
+        if (x < J.dof && J.act[x] >= 0)
+          g_act[(size_t)J.act[x] * E + e] = (raw[x] >= J.act_lo[x] && raw[x] <= J.act_hi[x]) ? ga[x] : 0.f;
+    if (b == 0)
+      for (int x = ty.na; x < Am; ++x) g_act[(size_t)x * E + e] = 0.f;
   }
 }
 

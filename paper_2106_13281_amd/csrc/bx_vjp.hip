@@ -657,9 +657,8 @@ __global__ __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(PAIRS ? 1 :
   }
 #undef BX_FWD
   block_exchange();
-  auto rec_at = [&](int, int sub) { return tape + (size_t)sub * TAPE_N * 64; };
 #define BX_ROLE(R, D)                                                                                                \
-  split_adj_run<R, D, PAIRS, REGC>(tab, wk, env_list, type_off, E, Bm, Am, act, g_out, g_in, g_act, 1, rec_at, A, pl)
+  split_adj_run<R, D, PAIRS, REGC>(tab, wk, env_list, type_off, E, Bm, Am, act, g_out, g_in, g_act, tape, A, pl)
   if (role == 0)
     BX_ROLE(0, 1);
   else if (role == 2)
