@@ -109,8 +109,9 @@ typedef struct {
   int32_t n_params[BRAX_MAX_TYPES];    /* system parameters per type (brax_step_vjp_params) */
   int32_t p_max;                       /* the largest of n_params */
   int32_t n_pairs[BRAX_MAX_TYPES];     /* body-body contact candidates per type */
-  int64_t vjp_lds_bytes;               /* on-chip memory per wavefront of the fused brax_step_vjp */
-  int64_t vjp_params_lds_bytes;        /* the same for brax_step_vjp_params */
+  int64_t vjp_lds_bytes;               /* the least on-chip memory per work item that a fused brax_step_vjp takes: a
+                                          batch where it exceeds lds_limit runs the per-phase adjoint */
+  int64_t vjp_params_lds_bytes;        /* the same for brax_step_vjp_params, which is fused only */
   int64_t lds_limit;                   /* the device's per-workgroup limit (160 KiB for a host-only handle) */
   int32_t lanes_per_env[BRAX_MAX_TYPES]; /* lanes per environment of the fused forward without a tape: one
                                             per body, plus one per two further ground-contact candidates of
@@ -175,9 +176,12 @@ int brax_step(const brax_sys* sys, const brax_state* in, const float* act, brax_
  * given g_out = dL/d(out), writes g_in = dL/d(in) and g_act = dL/d(act)
  * (overwritten, not accumulated) for the same function brax_step computes.
  * The forward substeps are recomputed inside. The fused adjoint keeps their
- * tape on chip (brax_layout.vjp_lds_bytes per wavefront); a batch whose
- * tape exceeds lds_limit (many substeps) runs the per-phase adjoint of
- * BRAX_PLAIN instead, whose tape lives in the handle's device workspace. At kinks the one-sided
+ * tape on chip (at least brax_layout.vjp_lds_bytes per work item); a batch
+ * whose tape exceeds lds_limit (many substeps) runs the per-phase adjoint of
+ * BRAX_PLAIN instead, whose tape lives in the handle's device workspace. Which
+ * fused kernel runs depends on the batch (its size, types and substep counts);
+ * the two round differently, so an environment's cotangents agree between
+ * batches up to rounding. One batch gives the same bits on every call. At kinks the one-sided
  * conventions are: max(0,x)' = [x > 0]; the Coulomb cap is taken when
  * cap <= stop; clamp' = 1 and clip' = 1 on the closed interval;
  * contact activation and counts have zero derivative. g_in may not alias
