@@ -688,6 +688,34 @@ static int autotune_impl(brax_sys* s, const brax_state* in, const float* act, in
   float best_total = 1e30f;
   int best_wpb = s->waves_per_block;
   std::vector<int> epw_c;
+  // the best of three runs of the shape in s->envs_per_wave with wpb
+  // wavefronts per block. On two wavefronts per item a block holds one item
+  // whatever wpb is: such a shape is timed once, so that timing noise picks no
+  // block shape
+  std::map<std::vector<int>, float> timed;
+  auto trial = [&](int wpb, float& acc) -> int {
+    const std::vector<int> key(s->envs_per_wave, s->envs_per_wave + s->n_types);
+    build_work(s);
+    const bool two = fused_takes_two(c, (int)s->work.size(), T, false);
+    const auto seen = timed.find(key);
+    if (two && seen != timed.end()) {
+      acc = seen->second;
+      return BRAX_OK;
+    }
+    int r = upload_work(s);
+    float ms = 0;
+    acc = 1e30f;
+    for (int rep = 0; rep < 3 && !r; ++rep) {
+      if (hipEventRecord(e0, st) != hipSuccess ||
+          launch_fused(c, s->d_work, (int)s->work.size(), wpb, a, b, acts, T, 0, Fields{}, false, st) != hipSuccess ||
+          hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+          hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
+        r = fail(BRAX_E_DEVICE, "autotune launch failed");
+      acc = std::min(acc, ms);
+    }
+    if (two && !r) timed[key] = acc;
+    return r;
+  };
   for (int wpb : wpb_c) {
     if (rc) break;
     for (int t = 0; t < s->n_types; ++t) {
@@ -716,18 +744,8 @@ static int autotune_impl(brax_sys* s, const brax_state* in, const float* act, in
         for (int u = 0; u < s->n_types; ++u) saved[u] = s->envs_per_wave[u];
         for (int u = 0; u < s->n_types; ++u) s->envs_per_wave[u] = best_epw[u];
         s->envs_per_wave[t] = epw;
-        build_work(s);
-        if ((rc = upload_work(s))) break;
-        float ms = 0, acc = 1e30f;
-        for (int rep = 0; rep < 3 && !rc; ++rep) {
-          if (hipEventRecord(e0, st) != hipSuccess ||
-              launch_fused(c, s->d_work, (int)s->work.size(), wpb, a, b, acts, T, 0, Fields{}, false, st) !=
-                  hipSuccess ||
-              hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-              hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
-            rc = fail(BRAX_E_DEVICE, "autotune launch failed");
-          acc = std::min(acc, ms);
-        }
+        float acc;
+        if ((rc = trial(wpb, acc))) break;
         for (int u = 0; u < s->n_types; ++u) s->envs_per_wave[u] = saved[u];
         // a later (emptier) shape must be faster by more than the timing
         // noise (1%), so that repeated tunings settle on the same shape
@@ -741,20 +759,9 @@ static int autotune_impl(brax_sys* s, const brax_state* in, const float* act, in
     if (rc) break;
     // whole batch at this block shape
     for (int u = 0; u < s->n_types; ++u) s->envs_per_wave[u] = best_epw[u];
-    build_work(s);
-    if ((rc = upload_work(s))) break;
-    float ms = 0, acc = 1e30f;
-    for (int rep = 0; rep < 3; ++rep) {
-      if (hipEventRecord(e0, st) != hipSuccess ||
-          launch_fused(c, s->d_work, (int)s->work.size(), wpb, a, b, acts, T, 0, Fields{}, false, st) != hipSuccess ||
-          hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-          hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
-        rc = fail(BRAX_E_DEVICE, "autotune launch failed");
-        break;
-      }
-      acc = std::min(acc, ms);
-    }
-    if (!rc && acc < 0.99f * best_total) {
+    float acc;
+    if ((rc = trial(wpb, acc))) break;
+    if (acc < 0.99f * best_total) {
       best_total = acc;
       best_wpb = wpb;
     }

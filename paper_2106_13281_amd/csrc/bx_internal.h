@@ -104,6 +104,10 @@ hipError_t launch_default_qp(const LaunchCtx& c, const float* angles, const floa
 hipError_t launch_fused(const LaunchCtx& c, const WaveWork* work, int n_work, int waves_per_block, Fields in,
                         Fields out, const float* acts, int T, int save_every, Fields traj, bool flags, hipStream_t s,
                         float* tape = nullptr, int smax = 0);
+// Whether launch_fused (and, with T = 1 and no tape, launch_env_step) runs
+// n_work work items on two wavefronts each, one item per block whatever
+// waves_per_block is.
+bool fused_takes_two(const LaunchCtx& c, int n_work, int T, bool tape);
 // Plain path: one step (all substeps) of every type; acts points at this
 // step's [Am][E] actions. jslot/cslot: per-type scratch. tape (nullable):
 // per substep [TAPE_N][Bm][E] records for the adjoint, see bx_access.h.

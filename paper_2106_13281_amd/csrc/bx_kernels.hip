@@ -851,6 +851,18 @@ static bool split_pays(const LaunchCtx& c, int n_work, bool pairs, int T, bool t
   return n_work <= (pairs ? 3 : T < (tape ? 2 : 4) ? 4 : 5) * c.n_cu;
 }
 
+bool fused_takes_two(const LaunchCtx& c, int n_work, int T, bool tape) {
+  bool pairs = false, many_lane_contacts = false, cl = false;
+  for (int t = 0; t < c.n_types; ++t) {
+    pairs = pairs || c.host_tab->type[t].np > 0;
+    many_lane_contacts = many_lane_contacts || c.host_tab->type[t].max_lc > REG_CONTACTS;  // contact lanes included
+    cl = cl || c.host_tab->type[t].nl > c.host_tab->type[t].nb;
+  }
+  // untaped, two candidates per lane in registers: with contact lanes further
+  // ones (of a type whose lanes did not fit) are read from the table
+  return split_pays(c, n_work, pairs, T, tape) && (tape || cl || !many_lane_contacts);
+}
+
 hipError_t launch_env_step(const LaunchCtx& c, const WaveWork* work, int n_work, int waves_per_block,
                            const EnvT* env, int Omax, Fields in, Fields out, const float* act, Fields reset, float* obs,
                            float* reward, uint8_t* done, bool flags, hipStream_t s) {
@@ -868,7 +880,7 @@ hipError_t launch_env_step(const LaunchCtx& c, const WaveWork* work, int n_work,
 #define BX_ENV(P, R, L)                                                                                            \
   hipLaunchKernelGGL((k_fused_env<P, R, L>), grid, block, lds, s, c.tab, work, n_work, c.env_list, c.type_off, c.E, \
                      c.Bm, in, out, act, c.Am, nf, ea)
-  if (split_pays(c, n_work, pairs, 1, false) && (cl || !many_contacts)) {
+  if (fused_takes_two(c, n_work, 1, false)) {
     const dim3 sgrid(n_work), sblock(128);
     const Fields none{nullptr, nullptr, nullptr, nullptr};
 #define BX_SPLIT(P, L)                                                                                             \
@@ -933,7 +945,7 @@ hipError_t launch_fused(const LaunchCtx& c, const WaveWork* work, int n_work, in
   // (further ones, of a type whose lanes did not fit, are read from the table)
   if (cl) many_lane_contacts = false;
   const size_t lds = fused_lds_per_wave(pairs) * waves_per_block;
-  if (split_pays(c, n_work, pairs, T, tape != nullptr) && (tape || !many_lane_contacts)) {
+  if (fused_takes_two(c, n_work, T, tape != nullptr)) {
     const dim3 grid(n_work), block(128);
     uint8_t* nf = flags ? c.nonfinite : nullptr;
     const EnvArgs none{};

@@ -101,3 +101,10 @@ def test_vjp_lds_limits_match_oracle(name, substeps):
     """The recomputing adjoint's LDS at 160 KiB: 32 substeps are the last on three wavefronts,
     33 and 36 the first and last on one, 37 the first per phase."""
     check_vjp(star(2, substeps) if name == "star" else text(name, substeps), 6, substeps)
+
+
+def test_autotune_picks_no_block_shape_by_noise():
+    """On two wavefronts per work item the block shape plays no part: the tuner's first stays."""
+    s = braxmi.System(synth.system_text("quadruped"), 700, device=0)
+    for _ in range(3):
+        assert s.autotune()[1] == 1
