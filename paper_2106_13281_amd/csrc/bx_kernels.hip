@@ -400,7 +400,7 @@ __device__ __forceinline__ void store_result(const Fields& out, const Body& s, i
 // final state), so that an environment step is one launch.
 // CL: the batch has contact lanes (see TypeT::nl); kernels for batches
 // without keep one lane per body and none of the lane-group code.
-template <int MAXDOF, bool TAPE, bool PAIRS, int REGC = REG_CONTACTS, bool ENV = false, bool CL = false>
+template <int MAXDOF, bool TAPE, bool PAIRS, int REGC, bool ENV, bool CL, bool STRAIGHT>
 __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const WaveWork& wk,
                                           const int32_t* __restrict__ env_list, const int32_t* __restrict__ type_off,
                                           int E, int Bm, const Fields& in, const Fields& out,
@@ -483,9 +483,8 @@ __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const 
       // need none of it)
       v3 dv = V(0.f, 0.f, 0.f), dw = V(0.f, 0.f, 0.f);
       int cnt = 0;
-      constexpr bool STRAIGHT = REGC == 2 && (!CL || PAIRS);
-      ground_contacts<REGC, STRAIGHT, STRAIGHT && !TAPE>(&tab->contact[t][cfirst], Creg, n_con, max_con, ty, B, s, f, dv, dw,
-                                                         cnt);
+      ground_contacts<REGC, STRAIGHT, STRAIGHT && !TAPE && (!CL || PAIRS)>(&tab->contact[t][cfirst], Creg, n_con, max_con,
+                                                                           ty, B, s, f, dv, dw, cnt);
       // joint evaluated on every lane (a root uses its own state as the
       // parent and its result is discarded)
       JointOut jo = joint_eval<MAXDOF>(J, P, RP, s, jc, a);
@@ -575,13 +574,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void
   if (w >= n_work) return;
   const WaveWork wk = work[w];
   XchRows* X = xch_lanes(fused_lds);
+  constexpr bool SC = straight_contacts(ONE_AXIS, false, CL, REGC);
   // wave-uniform: joints of at most one axis take the shorter path
   if (ONE_AXIS || tab->type[wk.type].max_dof <= 1)
-    fused_run<1, false, false, REGC, false, CL>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T,
-                                                save_every, traj, nonfinite, nullptr, 0, w, n_work, X);
+    fused_run<1, false, false, REGC, false, CL, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T,
+                                                    save_every, traj, nonfinite, nullptr, 0, w, n_work, X);
   else
-    fused_run<3, false, false, REGC, false, CL>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T,
-                                                save_every, traj, nonfinite, nullptr, 0, w, n_work, X);
+    fused_run<3, false, false, REGC, false, CL, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T,
+                                                    save_every, traj, nonfinite, nullptr, 0, w, n_work, X);
 }
 
 // The same with the forward tape: a kernel of its own, so that the tape
@@ -602,12 +602,13 @@ __global__ __launch_bounds__(256) void k_fused_tape(const Tables* __restrict__ t
   if (w >= n_work) return;
   const WaveWork wk = work[w];
   XchRows* X = xch_lanes(fused_lds);
+  constexpr bool SC = straight_contacts(false, false, false, REGC);
   if (tab->type[wk.type].max_dof <= 1)
-    fused_run<1, true, false, REGC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every, traj,
-                                    nonfinite, tape, smax, w, n_work, X);
+    fused_run<1, true, false, REGC, false, false, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
+                                                      traj, nonfinite, tape, smax, w, n_work, X);
   else
-    fused_run<3, true, false, REGC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every, traj,
-                                    nonfinite, tape, smax, w, n_work, X);
+    fused_run<3, true, false, REGC, false, false, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
+                                                      traj, nonfinite, tape, smax, w, n_work, X);
 }
 
 // The same for batches with body-body contacts: kernels of their own (with
@@ -629,18 +630,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   const WaveWork wk = work[w];
   XchRows* X = xch_lanes(fused_lds);
   PairLanes* pl = pair_lanes(fused_lds);
+  constexpr bool SC = straight_contacts(ONE_AXIS, true, CL, REGC);
   if (ONE_AXIS || tab->type[wk.type].max_dof <= 1)
-    fused_run<1, TAPE, true, REGC, false, CL>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
+    fused_run<1, TAPE, true, REGC, false, CL, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
                                               traj, nonfinite, tape, smax, w, n_work, X, pl);
   else
-    fused_run<3, TAPE, true, REGC, false, CL>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
+    fused_run<3, TAPE, true, REGC, false, CL, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
                                               traj, nonfinite, tape, smax, w, n_work, X, pl);
 }
 
 // One environment step with the environment layer fused after it (T = 1):
 // kernels of their own so that the epilogue's registers do not weigh on the
 // rollout kernels. PAIRS: batches with body-body candidates.
-template <bool PAIRS, int REGC, bool CL>
+template <bool PAIRS, int REGC, bool CL, bool SC = straight_contacts(false, PAIRS, CL, REGC)>
 __global__ __launch_bounds__(256) void k_fused_env(const Tables* __restrict__ tab, const WaveWork* __restrict__ work,
                                                    int n_work, const int32_t* __restrict__ env_list,
                                                    const int32_t* __restrict__ type_off, int E, int Bm, Fields in,
@@ -654,10 +656,10 @@ __global__ __launch_bounds__(256) void k_fused_env(const Tables* __restrict__ ta
   PairLanes* pl = PAIRS ? pair_lanes(fused_lds) : nullptr;
   const Fields none{nullptr, nullptr, nullptr, nullptr};
   if (tab->type[wk.type].max_dof <= 1)
-    fused_run<1, false, PAIRS, REGC, true, CL>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, 1, 0, none,
+    fused_run<1, false, PAIRS, REGC, true, CL, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, 1, 0, none,
                                                nonfinite, nullptr, 0, w, n_work, X, pl, &ea);
   else
-    fused_run<3, false, PAIRS, REGC, true, CL>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, 1, 0, none,
+    fused_run<3, false, PAIRS, REGC, true, CL, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, 1, 0, none,
                                                nonfinite, nullptr, 0, w, n_work, X, pl, &ea);
 }
 
@@ -665,7 +667,7 @@ __global__ __launch_bounds__(256) void k_fused_env(const Tables* __restrict__ ta
 // (see bx_split.h)
 // ROLE: 0 the joint wavefront, 1 the contact wavefront. The other parameters
 // as for fused_run (two contact candidates per lane in registers).
-template <int ROLE, int MAXDOF, bool TAPE, bool PAIRS, bool ENV, bool CL, int REGC>
+template <int ROLE, int MAXDOF, bool TAPE, bool PAIRS, bool ENV, bool CL, int REGC, bool STRAIGHT>
 __device__ __forceinline__ void split_run(const Tables* __restrict__ tab, const WaveWork& wk,
                                           const int32_t* __restrict__ env_list, const int32_t* __restrict__ type_off,
                                           int E, int Bm, const Fields& in, const Fields& out,
@@ -749,7 +751,7 @@ __device__ __forceinline__ void split_run(const Tables* __restrict__ tab, const 
       if (RECORD) wtape_state<true>(tp, s, lane);
       v3 torque;
       int cnt;
-      split_substep<ROLE, MAXDOF, PAIRS, CL, REGC, decltype(parity)::value>(tab, t, ty, B, J, has_joint, Creg, cfirst, n_con,
+      split_substep<ROLE, MAXDOF, PAIRS, CL, REGC, STRAIGHT, decltype(parity)::value>(tab, t, ty, B, J, has_joint, Creg, cfirst, n_con,
                                                                             max_con, lane, b, base, nl > nb, src_parent, csrc,
                                                                             a, s, L, XC, pl, ps0, torque, cnt);
       if (RECORD) wtape_torque<true>(tp, wz, torque, lane);
@@ -783,7 +785,8 @@ __device__ __forceinline__ void split_run(const Tables* __restrict__ tab, const 
 
 // One work item per block of two wavefronts (w is block-uniform: a block past
 // the list ends as a whole, before any barrier).
-template <bool ONE_AXIS, bool TAPE, bool PAIRS, bool ENV, bool CL, int REGC = REG_CONTACTS>
+template <bool ONE_AXIS, bool TAPE, bool PAIRS, bool ENV, bool CL, int REGC = REG_CONTACTS,
+          bool SC = straight_contacts(ONE_AXIS, PAIRS, CL, REGC)>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(PAIRS ? 2 : 3))) void k_split(const Tables* __restrict__ tab, const WaveWork* __restrict__ work,
                                                int n_work, const int32_t* __restrict__ env_list,
                                                const int32_t* __restrict__ type_off, int E, int Bm, Fields in,
@@ -799,7 +802,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(PAIRS ? 2 :
   PairLanes* pl = PAIRS ? reinterpret_cast<PairLanes*>(XC + 1) : nullptr;
   const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #define BX_ROLE(R, D)                                                                                              \
-  split_run<R, D, TAPE, PAIRS, ENV, CL, REGC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every, traj, \
+  split_run<R, D, TAPE, PAIRS, ENV, CL, REGC, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every, traj, \
                                         nonfinite, tape, smax, w, n_work, L, XC, pl, &ea)
   if (ONE_AXIS || tab->type[wk.type].max_dof <= 1) {
     if (role == 0)
@@ -867,9 +870,10 @@ hipError_t launch_env_step(const LaunchCtx& c, const WaveWork* work, int n_work,
                            const EnvT* env, int Omax, Fields in, Fields out, const float* act, Fields reset, float* obs,
                            float* reward, uint8_t* done, bool flags, hipStream_t s) {
   if (n_work == 0) return hipSuccess;
-  bool pairs = false, many_contacts = false, cl = false;
+  bool pairs = false, one_axis = true, many_contacts = false, cl = false;
   for (int t = 0; t < c.n_types; ++t) {
     pairs = pairs || c.host_tab->type[t].np > 0;
+    one_axis = one_axis && c.host_tab->type[t].max_dof <= 1;
     many_contacts = many_contacts || c.host_tab->type[t].max_lc > REG_CONTACTS;  // per lane, contact lanes included
     cl = cl || c.host_tab->type[t].nl > c.host_tab->type[t].nb;
   }
@@ -877,19 +881,21 @@ hipError_t launch_env_step(const LaunchCtx& c, const WaveWork* work, int n_work,
   uint8_t* nf = flags ? c.nonfinite : nullptr;
   const EnvArgs ea{env, reset, obs, reward, done, Omax};
   const size_t lds = fused_lds_per_wave(pairs) * waves_per_block;
-#define BX_ENV(P, R, L)                                                                                            \
-  hipLaunchKernelGGL((k_fused_env<P, R, L>), grid, block, lds, s, c.tab, work, n_work, c.env_list, c.type_off, c.E, \
+#define BX_ENV(P, R, ...)                                                                                          \
+  hipLaunchKernelGGL((k_fused_env<P, R, __VA_ARGS__>), grid, block, lds, s, c.tab, work, n_work, c.env_list, c.type_off, c.E, \
                      c.Bm, in, out, act, c.Am, nf, ea)
   if (fused_takes_two(c, n_work, 1, false)) {
     const dim3 sgrid(n_work), sblock(128);
     const Fields none{nullptr, nullptr, nullptr, nullptr};
-#define BX_SPLIT(P, L)                                                                                             \
-  hipLaunchKernelGGL((k_split<false, false, P, true, L>), sgrid, sblock, split_lds(pairs, cl), s, c.tab, work, n_work, \
+#define BX_SPLIT(P, ...)                                                                                             \
+  hipLaunchKernelGGL((k_split<false, false, P, true, __VA_ARGS__>), sgrid, sblock, split_lds(pairs, cl), s, c.tab, work, n_work, \
                      c.env_list, c.type_off, c.E, c.Bm, in, out, act, c.Am, 1, 0, none, nf, nullptr, 0, ea)
     if (pairs && cl)
       BX_SPLIT(true, true);
     else if (pairs)
       BX_SPLIT(true, false);
+    else if (cl && one_axis)
+      BX_SPLIT(false, true, REG_CONTACTS, straight_contacts(true, false, true, REG_CONTACTS));
     else if (cl)
       BX_SPLIT(false, true);
     else
@@ -902,6 +908,8 @@ hipError_t launch_env_step(const LaunchCtx& c, const WaveWork* work, int n_work,
     BX_ENV(true, REG_CONTACTS, true);
   else if (pairs)
     BX_ENV(true, REG_CONTACTS, false);
+  else if (cl && one_axis)
+    BX_ENV(false, REG_CONTACTS, true, straight_contacts(true, false, true, REG_CONTACTS));
   else if (cl)
     BX_ENV(false, REG_CONTACTS, true);
   else if (many_contacts)

@@ -8,18 +8,24 @@
 
 namespace bx {
 
+// Where the impulses run without branches: kernels that hold two candidates,
+// but not those for one-axis batches with contact lanes. There, and with eight
+// candidates, most slots have a few lanes of one body in them and the branches
+// are the faster form: manipulator x 20 steps, branches -> straight, one wavefront
+// per item 12240 environments 341 -> 354 us, taped 18360 444 -> 530, two wavefronts
+// 7674 303 -> 315, taped 11511 397 -> 476; mixed batch of 13600, taped 385 -> 414.
+// The mixed batch untaped, whose other types have no such body: 4096 x 100 steps
+// 1078 -> 1100, 8000 1291 -> 1276, 10232 1467 -> 1436. With body-body contacts (and
+// the penetrating first) grasp 14040 x 20 steps 1199 -> 1172.
+constexpr bool straight_contacts(bool one_axis, bool pairs, bool cl, int regc) {
+  return regc == REG_CONTACTS && (pairs || !cl || !one_axis);
+}
+
 // A lane's ground-contact candidates: the first REGC from registers (no
 // dynamic indexing; a slot no body of the type has is skipped by the whole
 // wave), the rest from the table C. Adds the velocity changes to dv, dw and
 // the applied candidates to cnt.
-// STRAIGHT: the impulses without branches (contact_add, the same sums), in
-// kernels that hold two candidates and no contact lanes, and in those with
-// body-body contacts (grasp 14040 environments x 20 steps, branches -> straight
-// with the penetrating first: 1199 -> 1172 us). With eight candidates or with contact lanes most slots
-// have a few lanes of one body in them, and the branches are the faster form:
-// manipulator x 20 steps, branches -> straight, one wavefront per item 12240
-// environments 341 -> 354 us, taped 18360 444 -> 530, two wavefronts 7674 303 ->
-// 315, taped 11511 397 -> 476.
+// STRAIGHT: the impulses without branches (contact_add, the same sums).
 // PEN_FIRST (of STRAIGHT kernels): the penetrating candidates first, in
 // candidate order (the same sums), so that the second evaluation runs only
 // where a lane has two penetrating candidates, not wherever one has its second
@@ -133,7 +139,7 @@ constexpr int tape_role(int maxdof) { return maxdof > 1 ? 1 : 0; }
 // use different ones. csrc: the children's mail rows (64: the zero row).
 // groups: the batch has contact lanes in this type. torque: the body's total
 // torque; cnt (ROLE 1): its applied contacts.
-template <int ROLE, int MAXDOF, bool PAIRS, bool CL, int REGC, int PAR>
+template <int ROLE, int MAXDOF, bool PAIRS, bool CL, int REGC, bool STRAIGHT, int PAR>
 __device__ __forceinline__ void split_substep(const Tables* __restrict__ tab, int t, const TypeT& ty, const BodyT& B,
                                               const JointT& J, bool has_joint, const ContactT (&Creg)[REGC], int cfirst,
                                               int n_con, int max_con, int lane, int b, int base, bool groups,
@@ -172,8 +178,7 @@ __device__ __forceinline__ void split_substep(const Tables* __restrict__ tab, in
       near0 = pair_near0(XC, *pl, ps0);
     }
     const Frame f = derive_inv(B, R);
-    constexpr bool STRAIGHT = REGC == 2 && (!CL || PAIRS);
-    ground_contacts<REGC, STRAIGHT, STRAIGHT>(&tab->contact[t][cfirst], Creg, n_con, max_con, ty, B, s, f, dv, dw, cnt);
+    ground_contacts<REGC, STRAIGHT, STRAIGHT && REGC == 2 && (!CL || PAIRS)>(&tab->contact[t][cfirst], Creg, n_con, max_con, ty, B, s, f, dv, dw, cnt);
     gyro = gyro_torque(B, s, f);
     if (groups) lane_group_sums(XC, lane, base, b, ty, B, dv, dw, cnt);
     if (PAIRS && ty.np > 0) pair_phase(tab, t, *pl, XC, lane, b, base, s, f, dv, dw, cnt, near0);
