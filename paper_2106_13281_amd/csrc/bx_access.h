@@ -228,12 +228,12 @@ __device__ __forceinline__ void contact_add(float rho, const TypeT& ty, const Bo
   // a product with NaN would carry it into the other components
   const bool slip = sp2 > 0.f;
   const float isp = __builtin_amdgcn_rsqf(sp2);
-  const float tx = slip ? u.x * isp : 0.f, ty_ = slip ? u.y * isp : 0.f, sp = slip ? sp2 * isp : 0.f;
+  const float tx = slip ? u.x * isp : 0.f, ty_ = slip ? u.y * isp : 0.f, sp = sp2 * isp;
   const v3 z = V(-(r.z * ty_), r.z * tx, fmaf(r.x, ty_, -(r.y * tx)));
   const v3 bz = mul(I, z);
   const float kt = B.inv_m + dot(z, bz);
   const float stop = sp * __builtin_amdgcn_rcpf(kt), cap = ty.mu * jn;
-  const float jt = cap <= stop ? cap : stop;
+  const float jt = slip ? (cap <= stop ? cap : stop) : 0.f;
   v3 dwc = V(fmaf(-bz.x, jt, jn * a.x), fmaf(-bz.y, jt, jn * a.y), fmaf(-bz.z, jt, jn * a.z));
   pin(dwc);  // rounded before it is added, as in contact_apply
   dv.x = on ? fmaf(B.inv_m, -(jt * tx), dv.x) : dv.x;
