@@ -37,21 +37,23 @@ __device__ __forceinline__ void store_body(const Fields& f, size_t base, const B
   f.ang[base + (2 * Bm + b) * E + e] = s.w.z;
 }
 
-// Trajectory snapshots are laid out like the state with a leading save index;
-// `base` is the element offset of snapshot k of a 3-component field, scaled
-// per field by the component count.
-__device__ __forceinline__ void store_snapshot(const Fields& f, size_t k, const Body& s, int b, int e, int Bm,
-                                               int E) {
-  size_t n3 = (size_t)3 * Bm * E, n4 = (size_t)4 * Bm * E;
-  Fields g{f.pos + k * n3, f.rot + k * n4, f.vel + k * n3, f.ang + k * n3};
-  store_body(g, 0, s, b, e, Bm, E);
-}
-
 __device__ __forceinline__ void zero_body(const Fields& f, int b, int e, int Bm, int E) {
   Body z;
   z.p = z.v = z.w = V(0.f, 0.f, 0.f);
   z.q = q4{0.f, 0.f, 0.f, 0.f};
   store_body(f, 0, z, b, e, Bm, E);
+}
+
+// The k-th snapshot of body lane b (trajectories are laid out like the state,
+// with a leading save index); the padded body slots of a system of nb bodies
+// are written as zeros.
+__device__ __forceinline__ void store_snapshot(const Fields& f, size_t k, const Body& s, int nb, int b, int e, int Bm,
+                                               int E) {
+  size_t n3 = (size_t)3 * Bm * E, n4 = (size_t)4 * Bm * E;
+  Fields g{f.pos + k * n3, f.rot + k * n4, f.vel + k * n3, f.ang + k * n3};
+  store_body(g, 0, s, b, e, Bm, E);
+  if (nb < Bm)  // wave-uniform
+    for (int pb = nb + b; pb < Bm; pb += nb) zero_body(g, pb, e, Bm, E);
 }
 
 // Tape of the fused path, wavefront-major: per substep and work item a record

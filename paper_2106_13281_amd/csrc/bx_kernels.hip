@@ -535,7 +535,7 @@ __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const 
       }
     }
     if (save_every > 0 && (step + 1) % save_every == 0) {
-      if (live && b < nb) store_snapshot(traj, (size_t)n_save, s, b, e, Bm, E);
+      if (live && b < nb) store_snapshot(traj, (size_t)n_save, s, nb, b, e, Bm, E);
       ++n_save;
     }
   }
@@ -766,7 +766,7 @@ __device__ __forceinline__ void split_run(const Tables* __restrict__ tab, const 
         block_exchange();  // an odd count: the next step starts on the rows just read
     }
     if (CONTACT && save_every > 0 && (step + 1) % save_every == 0) {
-      if (live && b < nb) store_snapshot(traj, (size_t)n_save, s, b, e, Bm, E);
+      if (live && b < nb) store_snapshot(traj, (size_t)n_save, s, nb, b, e, Bm, E);
       ++n_save;
     }
   }

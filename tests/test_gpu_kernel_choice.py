@@ -108,3 +108,20 @@ def test_autotune_picks_no_block_shape_by_noise():
     s = braxmi.System(synth.system_text("quadruped"), 700, device=0)
     for _ in range(3):
         assert s.autotune()[1] == 1
+
+
+@pytest.mark.parametrize("E", [40, 12000])  # two wavefronts per work item, one
+@pytest.mark.parametrize("flags", [braxmi.BRAX_FUSED, braxmi.BRAX_PLAIN])
+def test_trajectory_pads_with_zeros(E, flags):
+    """A trajectory's body slots beyond a system's bodies are written as zeros, as every state's."""
+    names = list(synth.MIXED_TYPES)
+    s = braxmi.System([synth.system_text(n) for n in names], E, env_desc=(torch.arange(E) % len(names)).tolist(), device=0)
+    x, acts = s.default_qp(), (torch.rand(3, s.a_max, E, generator=torch.Generator().manual_seed(8)) * 2 - 1).cuda()
+    traj = s.new_state(lead=(3,))
+    for f in traj.fields():
+        f.fill_(float("nan"))
+    s.rollout(x, acts, save_every=1, traj=traj, flags=flags)
+    for t, n in enumerate(names):
+        nb = oracle.Oracle(synth.system_text(n)).system.nb
+        for f in traj.fields():
+            assert torch.isfinite(f[:, :, :nb, t::len(names)]).all() and (f[:, :, nb:, t::len(names)] == 0).all()
