@@ -44,16 +44,10 @@ __device__ __forceinline__ void zero_body(const Fields& f, int b, int e, int Bm,
   store_body(f, 0, z, b, e, Bm, E);
 }
 
-// The k-th snapshot of body lane b (trajectories are laid out like the state,
-// with a leading save index); the padded body slots of a system of nb bodies
-// are written as zeros.
-__device__ __forceinline__ void store_snapshot(const Fields& f, size_t k, const Body& s, int nb, int b, int e, int Bm,
-                                               int E) {
-  size_t n3 = (size_t)3 * Bm * E, n4 = (size_t)4 * Bm * E;
-  Fields g{f.pos + k * n3, f.rot + k * n4, f.vel + k * n3, f.ang + k * n3};
-  store_body(g, 0, s, b, e, Bm, E);
-  if (nb < Bm)  // wave-uniform
-    for (int pb = nb + b; pb < Bm; pb += nb) zero_body(g, pb, e, Bm, E);
+// Trajectories are laid out like the state, with a leading save index.
+__device__ __forceinline__ Fields snapshot(const Fields& f, size_t k, int Bm, int E) {
+  const size_t n3 = (size_t)3 * Bm * E, n4 = (size_t)4 * Bm * E;
+  return Fields{f.pos + k * n3, f.rot + k * n4, f.vel + k * n3, f.ang + k * n3};
 }
 
 // Tape of the fused path, wavefront-major: per substep and work item a record
