@@ -682,6 +682,8 @@ static int autotune_impl(brax_sys* s, const brax_state* in, const float* act, in
   }
   const int n_simd = 4 * s->n_cu;  // four SIMDs per compute unit
   // candidates: environments per wavefront (per type) and wavefronts per block
+  // (each block shape times the environments per wavefront anew: the first trials
+  // run on idle clocks)
   const int wpb_c[] = {1, 2, 4};
   int best_epw[MAXT];
   for (int t = 0; t < s->n_types; ++t) best_epw[t] = s->envs_per_wave[t];
@@ -689,19 +691,9 @@ static int autotune_impl(brax_sys* s, const brax_state* in, const float* act, in
   int best_wpb = s->waves_per_block;
   std::vector<int> epw_c;
   // the best of three runs of the shape in s->envs_per_wave with wpb
-  // wavefronts per block. On two wavefronts per item a block holds one item
-  // whatever wpb is: such a shape is timed once, so that timing noise picks no
-  // block shape
-  std::map<std::vector<int>, float> timed;
+  // wavefronts per block
   auto trial = [&](int wpb, float& acc) -> int {
-    const std::vector<int> key(s->envs_per_wave, s->envs_per_wave + s->n_types);
     build_work(s);
-    const bool two = fused_takes_two(c, (int)s->work.size(), T, false);
-    const auto seen = timed.find(key);
-    if (two && seen != timed.end()) {
-      acc = seen->second;
-      return BRAX_OK;
-    }
     int r = upload_work(s);
     float ms = 0;
     acc = 1e30f;
@@ -713,7 +705,6 @@ static int autotune_impl(brax_sys* s, const brax_state* in, const float* act, in
         r = fail(BRAX_E_DEVICE, "autotune launch failed");
       acc = std::min(acc, ms);
     }
-    if (two && !r) timed[key] = acc;
     return r;
   };
   for (int wpb : wpb_c) {
@@ -763,7 +754,9 @@ static int autotune_impl(brax_sys* s, const brax_state* in, const float* act, in
     if ((rc = trial(wpb, acc))) break;
     if (acc < 0.99f * best_total) {
       best_total = acc;
-      best_wpb = wpb;
+      // on two wavefronts per item a block holds one item whatever wpb is:
+      // no block shape is kept for such a launch by timing noise
+      best_wpb = fused_takes_two(c, (int)s->work.size(), T, false) ? 1 : wpb;
     }
   }
   if (!rc) {
