@@ -202,45 +202,66 @@ __device__ __forceinline__ void pin(v3& a) {
   pin(a.z);
 }
 
-// contact_apply (the same values, also on a non-finite slip) without branches,
-// for the lanes of a wavefront together: a lane whose candidate does not
-// penetrate (in = false) or takes no impulse keeps its sums by selects. The
-// branches cost more than the lanes they skip (7 zeroed registers and three
-// scalar instructions each, and a wavefront of several environments nearly
-// always has a lane in contact): 100 steps, branches -> straight, quadruped 4102
-// environments 912 -> 872 us, planar runner 5274 744 -> 698, chain 12306 939 -> 842,
-// biped 11705 2659 -> 2521; where it does not pay, straight_contacts. Terms with the zero components of z and t
-// are left out, and divisions take the reciprocal directly (exact scaling by
-// 1 for denominators up to 2^96).
+// contact_apply (the same values, also on a non-finite slip) in three forms.
+// Terms with the zero components of z and t are left out, and divisions take
+// the reciprocal directly (exact scaling by 1 for denominators up to 2^96).
+// STRAIGHT: without branches, for the lanes of a wavefront together: a lane
+// whose candidate does not penetrate (in = false) or takes no impulse keeps its
+// sums by selects. The branches cost more than the lanes they skip (7 zeroed
+// registers and three scalar instructions each, and a wavefront of several
+// environments nearly always has a lane in contact): 100 steps, branches ->
+// straight, quadruped 4102 environments 912 -> 872 us, planar runner 5274 744 ->
+// 698, chain 12306 939 -> 842, biped 11705 2659 -> 2521; where it does not pay,
+// contact_form.
+// LANES: for the penetrating lanes alone (called under if (in)), straight up to
+// the sums. LANES_SKIP: the same with the impulse and friction behind branches.
+enum ContactForm { STRAIGHT, LANES, LANES_SKIP };
+template <ContactForm FORM>
 __device__ __forceinline__ void contact_add(float rho, const TypeT& ty, const BodyT& B, const Body& s, const s3& I, v3 rl,
                                             float depth, bool in, v3& dv, v3& dw, int& cnt) {
   const v3 r = V(rl.x, rl.y, rl.z - rho);
   const v3 u = s.v + cross(s.w, r);
-  const v3 a = V(fmaf(I.xx, r.y, -(I.xy * r.x)), fmaf(I.xy, r.y, -(I.yy * r.x)), fmaf(I.xz, r.y, -(I.yz * r.x)));
-  const float kn = B.inv_m + fmaf(a.x, r.y, -(a.y * r.x));
   const float num = fmaf(ty.beta_h, depth, -(ty.one_plus_e * u.z));
   const bool on = in && num > 0.f;
+  if (FORM == LANES_SKIP && !on) return;
+  const v3 a = V(fmaf(I.xx, r.y, -(I.xy * r.x)), fmaf(I.xy, r.y, -(I.yy * r.x)), fmaf(I.xz, r.y, -(I.yz * r.x)));
+  const float kn = B.inv_m + fmaf(a.x, r.y, -(a.y * r.x));
   const float jn = num * __builtin_amdgcn_rcpf(kn);
+  v3 dwc = jn * a;
+  float jx = 0.f, jy = 0.f;
   const float sp2 = fmaf(u.x, u.x, u.y * u.y);
-  // no friction where the slip is zero or NaN: t = 0 and jt = 0 by selects, as
-  // a product with NaN would carry it into the other components
+  // no friction where the slip is zero or NaN: t = 0 and jt = 0, without the
+  // branch by selects, as a product with NaN would carry it into the other
+  // components
   const bool slip = sp2 > 0.f;
-  const float isp = __builtin_amdgcn_rsqf(sp2);
-  const float tx = slip ? u.x * isp : 0.f, ty_ = slip ? u.y * isp : 0.f, sp = sp2 * isp;
-  const v3 z = V(-(r.z * ty_), r.z * tx, fmaf(r.x, ty_, -(r.y * tx)));
-  const v3 bz = mul(I, z);
-  const float kt = B.inv_m + dot(z, bz);
-  const float stop = sp * __builtin_amdgcn_rcpf(kt), cap = ty.mu * jn;
-  const float jt = slip ? (cap <= stop ? cap : stop) : 0.f;
-  v3 dwc = V(fmaf(-bz.x, jt, jn * a.x), fmaf(-bz.y, jt, jn * a.y), fmaf(-bz.z, jt, jn * a.z));
+  if (FORM != LANES_SKIP || slip) {
+    const float isp = __builtin_amdgcn_rsqf(sp2), sp = sp2 * isp;
+    const float tx = slip ? u.x * isp : 0.f, ty_ = slip ? u.y * isp : 0.f;
+    const v3 z = V(-(r.z * ty_), r.z * tx, fmaf(r.x, ty_, -(r.y * tx)));
+    const v3 bz = mul(I, z);
+    const float kt = B.inv_m + dot(z, bz);
+    const float stop = sp * __builtin_amdgcn_rcpf(kt), cap = ty.mu * jn;
+    const float jt = slip ? (cap <= stop ? cap : stop) : 0.f;
+    dwc = V(fmaf(-bz.x, jt, dwc.x), fmaf(-bz.y, jt, dwc.y), fmaf(-bz.z, jt, dwc.z));
+    jx = -(jt * tx);
+    jy = -(jt * ty_);
+  }
   pin(dwc);  // rounded before it is added, as in contact_apply
-  dv.x = on ? fmaf(B.inv_m, -(jt * tx), dv.x) : dv.x;
-  dv.y = on ? fmaf(B.inv_m, -(jt * ty_), dv.y) : dv.y;
-  dv.z = on ? fmaf(B.inv_m, jn, dv.z) : dv.z;
-  dw.x = on ? dw.x + dwc.x : dw.x;
-  dw.y = on ? dw.y + dwc.y : dw.y;
-  dw.z = on ? dw.z + dwc.z : dw.z;
-  cnt = on ? cnt + 1 : cnt;
+  if (FORM == STRAIGHT) {
+    dv.x = on ? fmaf(B.inv_m, jx, dv.x) : dv.x;
+    dv.y = on ? fmaf(B.inv_m, jy, dv.y) : dv.y;
+    dv.z = on ? fmaf(B.inv_m, jn, dv.z) : dv.z;
+    dw.x = on ? dw.x + dwc.x : dw.x;
+    dw.y = on ? dw.y + dwc.y : dw.y;
+    dw.z = on ? dw.z + dwc.z : dw.z;
+    cnt = on ? cnt + 1 : cnt;
+  } else if (on) {
+    dv.x = fmaf(B.inv_m, jx, dv.x);
+    dv.y = fmaf(B.inv_m, jy, dv.y);
+    dv.z = fmaf(B.inv_m, jn, dv.z);
+    dw += dwc;
+    ++cnt;
+  }
 }
 
 // Per-lane constants copied once into registers.

@@ -406,7 +406,7 @@ __device__ __forceinline__ void store_result(const Fields& out, const Body& s, i
 // final state), so that an environment step is one launch.
 // CL: the batch has contact lanes (see TypeT::nl); kernels for batches
 // without keep one lane per body and none of the lane-group code.
-template <int MAXDOF, bool TAPE, bool PAIRS, int REGC, bool ENV, bool CL, bool STRAIGHT>
+template <int MAXDOF, bool TAPE, bool PAIRS, int REGC, bool ENV, bool CL, ContactForm FORM>
 __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const WaveWork& wk,
                                           const int32_t* __restrict__ env_list, const int32_t* __restrict__ type_off,
                                           int E, int Bm, const Fields& in, const Fields& out,
@@ -489,7 +489,7 @@ __device__ __forceinline__ void fused_run(const Tables* __restrict__ tab, const 
       // need none of it)
       v3 dv = V(0.f, 0.f, 0.f), dw = V(0.f, 0.f, 0.f);
       int cnt = 0;
-      ground_contacts<REGC, STRAIGHT, STRAIGHT && !TAPE && (!CL || PAIRS)>(&tab->contact[t][cfirst], Creg, n_con, max_con,
+      ground_contacts<REGC, FORM, FORM == STRAIGHT && !TAPE && (!CL || PAIRS)>(&tab->contact[t][cfirst], Creg, n_con, max_con,
                                                                            ty, B, s, f, dv, dw, cnt);
       // joint evaluated on every lane (a root uses its own state as the
       // parent and its result is discarded)
@@ -580,13 +580,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void
   if (w >= n_work) return;
   const WaveWork wk = work[w];
   XchRows* X = xch_lanes(fused_lds);
-  constexpr bool SC = straight_contacts(ONE_AXIS, false, CL, REGC);
+  constexpr ContactForm FORM = contact_form(false, ONE_AXIS, false, CL, REGC);
   // wave-uniform: joints of at most one axis take the shorter path
   if (ONE_AXIS || tab->type[wk.type].max_dof <= 1)
-    fused_run<1, false, false, REGC, false, CL, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T,
+    fused_run<1, false, false, REGC, false, CL, FORM>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T,
                                                     save_every, traj, nonfinite, nullptr, 0, w, n_work, X);
   else
-    fused_run<3, false, false, REGC, false, CL, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T,
+    fused_run<3, false, false, REGC, false, CL, FORM>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T,
                                                     save_every, traj, nonfinite, nullptr, 0, w, n_work, X);
 }
 
@@ -608,12 +608,12 @@ __global__ __launch_bounds__(256) void k_fused_tape(const Tables* __restrict__ t
   if (w >= n_work) return;
   const WaveWork wk = work[w];
   XchRows* X = xch_lanes(fused_lds);
-  constexpr bool SC = straight_contacts(false, false, false, REGC);
+  constexpr ContactForm FORM = contact_form(false, false, false, false, REGC);
   if (tab->type[wk.type].max_dof <= 1)
-    fused_run<1, true, false, REGC, false, false, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
+    fused_run<1, true, false, REGC, false, false, FORM>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
                                                       traj, nonfinite, tape, smax, w, n_work, X);
   else
-    fused_run<3, true, false, REGC, false, false, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
+    fused_run<3, true, false, REGC, false, false, FORM>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
                                                       traj, nonfinite, tape, smax, w, n_work, X);
 }
 
@@ -636,19 +636,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   const WaveWork wk = work[w];
   XchRows* X = xch_lanes(fused_lds);
   PairLanes* pl = pair_lanes(fused_lds);
-  constexpr bool SC = straight_contacts(ONE_AXIS, true, CL, REGC);
+  constexpr ContactForm FORM = contact_form(false, ONE_AXIS, true, CL, REGC);
   if (ONE_AXIS || tab->type[wk.type].max_dof <= 1)
-    fused_run<1, TAPE, true, REGC, false, CL, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
+    fused_run<1, TAPE, true, REGC, false, CL, FORM>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
                                               traj, nonfinite, tape, smax, w, n_work, X, pl);
   else
-    fused_run<3, TAPE, true, REGC, false, CL, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
+    fused_run<3, TAPE, true, REGC, false, CL, FORM>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every,
                                               traj, nonfinite, tape, smax, w, n_work, X, pl);
 }
 
 // One environment step with the environment layer fused after it (T = 1):
 // kernels of their own so that the epilogue's registers do not weigh on the
 // rollout kernels. PAIRS: batches with body-body candidates.
-template <bool PAIRS, int REGC, bool CL, bool SC = straight_contacts(false, PAIRS, CL, REGC)>
+template <bool PAIRS, int REGC, bool CL, ContactForm FORM = contact_form(false, false, PAIRS, CL, REGC)>
 __global__ __launch_bounds__(256) void k_fused_env(const Tables* __restrict__ tab, const WaveWork* __restrict__ work,
                                                    int n_work, const int32_t* __restrict__ env_list,
                                                    const int32_t* __restrict__ type_off, int E, int Bm, Fields in,
@@ -662,10 +662,10 @@ __global__ __launch_bounds__(256) void k_fused_env(const Tables* __restrict__ ta
   PairLanes* pl = PAIRS ? pair_lanes(fused_lds) : nullptr;
   const Fields none{nullptr, nullptr, nullptr, nullptr};
   if (tab->type[wk.type].max_dof <= 1)
-    fused_run<1, false, PAIRS, REGC, true, CL, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, 1, 0, none,
+    fused_run<1, false, PAIRS, REGC, true, CL, FORM>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, 1, 0, none,
                                                nonfinite, nullptr, 0, w, n_work, X, pl, &ea);
   else
-    fused_run<3, false, PAIRS, REGC, true, CL, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, 1, 0, none,
+    fused_run<3, false, PAIRS, REGC, true, CL, FORM>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, 1, 0, none,
                                                nonfinite, nullptr, 0, w, n_work, X, pl, &ea);
 }
 
@@ -673,7 +673,7 @@ __global__ __launch_bounds__(256) void k_fused_env(const Tables* __restrict__ ta
 // (see bx_split.h)
 // ROLE: 0 the joint wavefront, 1 the contact wavefront. The other parameters
 // as for fused_run (two contact candidates per lane in registers).
-template <int ROLE, int MAXDOF, bool TAPE, bool PAIRS, bool ENV, bool CL, int REGC, bool STRAIGHT>
+template <int ROLE, int MAXDOF, bool TAPE, bool PAIRS, bool ENV, bool CL, int REGC, ContactForm FORM>
 __device__ __forceinline__ void split_run(const Tables* __restrict__ tab, const WaveWork& wk,
                                           const int32_t* __restrict__ env_list, const int32_t* __restrict__ type_off,
                                           int E, int Bm, const Fields& in, const Fields& out,
@@ -757,7 +757,7 @@ __device__ __forceinline__ void split_run(const Tables* __restrict__ tab, const 
       if (RECORD) wtape_state<true>(tp, s, lane);
       v3 torque;
       int cnt;
-      split_substep<ROLE, MAXDOF, PAIRS, CL, REGC, STRAIGHT, decltype(parity)::value>(tab, t, ty, B, J, has_joint, Creg, cfirst, n_con,
+      split_substep<ROLE, MAXDOF, PAIRS, CL, REGC, FORM, decltype(parity)::value>(tab, t, ty, B, J, has_joint, Creg, cfirst, n_con,
                                                                             max_con, lane, b, base, nl > nb, src_parent, csrc,
                                                                             a, s, L, XC, pl, ps0, torque, cnt);
       if (RECORD) wtape_torque<true>(tp, wz, torque, lane);
@@ -796,7 +796,7 @@ __device__ __forceinline__ void split_run(const Tables* __restrict__ tab, const 
 // the environment step with 12 to 20 B of scratch and 40 to 100 SGPRs spilled to
 // VGPR lanes in each.
 template <bool ONE_AXIS, bool TAPE, bool PAIRS, bool ENV, bool CL, int REGC = REG_CONTACTS,
-          bool SC = straight_contacts(ONE_AXIS, PAIRS, CL, REGC)>
+          ContactForm FORM = contact_form(true, ONE_AXIS, PAIRS, CL, REGC)>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(PAIRS ? 2 : 3))) void k_split(const Tables* __restrict__ tab, const WaveWork* __restrict__ work,
                                                int n_work, const int32_t* __restrict__ env_list,
                                                const int32_t* __restrict__ type_off, int E, int Bm, Fields in,
@@ -812,7 +812,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(PAIRS ? 2 :
   PairLanes* pl = PAIRS ? reinterpret_cast<PairLanes*>(XC + 1) : nullptr;
   const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #define BX_ROLE(R, D)                                                                                              \
-  split_run<R, D, TAPE, PAIRS, ENV, CL, REGC, SC>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every, traj, \
+  split_run<R, D, TAPE, PAIRS, ENV, CL, REGC, FORM>(tab, wk, env_list, type_off, E, Bm, in, out, acts, Am, T, save_every, traj, \
                                         nonfinite, tape, smax, w, n_work, L, XC, pl, &ea)
   if (ONE_AXIS || tab->type[wk.type].max_dof <= 1) {
     if (role == 0)
@@ -905,7 +905,7 @@ hipError_t launch_env_step(const LaunchCtx& c, const WaveWork* work, int n_work,
     else if (pairs)
       BX_SPLIT(true, false);
     else if (cl && one_axis)
-      BX_SPLIT(false, true, REG_CONTACTS, straight_contacts(true, false, true, REG_CONTACTS));
+      BX_SPLIT(false, true, REG_CONTACTS, contact_form(true, true, false, true, REG_CONTACTS));
     else if (cl)
       BX_SPLIT(false, true);
     else
@@ -919,7 +919,7 @@ hipError_t launch_env_step(const LaunchCtx& c, const WaveWork* work, int n_work,
   else if (pairs)
     BX_ENV(true, REG_CONTACTS, false);
   else if (cl && one_axis)
-    BX_ENV(false, REG_CONTACTS, true, straight_contacts(true, false, true, REG_CONTACTS));
+    BX_ENV(false, REG_CONTACTS, true, contact_form(false, true, false, true, REG_CONTACTS));
   else if (cl)
     BX_ENV(false, REG_CONTACTS, true);
   else if (many_contacts)

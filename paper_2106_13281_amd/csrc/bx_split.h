@@ -8,47 +8,48 @@
 
 namespace bx {
 
-// Where the impulses run without branches: kernels that hold two candidates,
-// but not those for one-axis batches with contact lanes. There, and with eight
-// candidates, most slots have a few lanes of one body in them and the branches
-// are the faster form: manipulator x 20 steps, branches -> straight, one wavefront
-// per item 12240 environments 341 -> 354 us, taped 18360 444 -> 530, two wavefronts
-// 7674 303 -> 315, taped 11511 397 -> 476; mixed batch of 13600, taped 385 -> 414.
-// The mixed batch untaped, whose other types have no such body: 4096 x 100 steps
-// 1078 -> 1100, 8000 1291 -> 1276, 10232 1467 -> 1436. With body-body contacts (and
-// the penetrating first) grasp 14040 x 20 steps 1199 -> 1172.
-constexpr bool straight_contacts(bool one_axis, bool pairs, bool cl, int regc) {
-  return regc == REG_CONTACTS && (pairs || !cl || !one_axis);
+// The form of the ground impulses. Straight in kernels that hold two candidates,
+// but not those for one-axis batches with contact lanes: there, and with eight
+// candidates, most slots have a few lanes of one body in them. On two wavefronts
+// per item (two) the chain counts, and the lanes in contact run straight
+// through; on one, two per SIMD share the issue slots, and skipped friction (a
+// box at rest) is time. Measured, contact_apply / STRAIGHT / LANES / LANES_SKIP (us):
+//   manipulator x 20 steps, boxes tumbling: taped, two wavefronts 4000 environments
+//     353 / 334 / 316 / 340, one 14000 478 / 503 / 486 / 484; untaped, two 4000 243 / 236 /
+//     231 / 231, one 14000 437 / 436 / 422 / 425
+//   boxes at rest: taped 9000 340 / 388 / 366 / 337, 15300 429 / 521 / 502 / 442;
+//     untaped 6000 255 / 263 / 263 / 255, 10200 337 / 352 / 354 / 333
+// The mixed batch untaped (only one of its types has such a body): 8000 x 100 steps
+// contact_apply 1291, STRAIGHT 1276. With body-body contacts (and the penetrating
+// first) grasp 14040 x 20 steps 1199, 1172.
+constexpr ContactForm contact_form(bool two, bool one_axis, bool pairs, bool cl, int regc) {
+  return regc == REG_CONTACTS && (pairs || !cl || !one_axis) ? STRAIGHT : two ? LANES : LANES_SKIP;
 }
 
 // A lane's ground-contact candidates: the first REGC from registers (no
 // dynamic indexing; a slot no body of the type has is skipped by the whole
 // wave), the rest from the table C. Adds the velocity changes to dv, dw and
 // the applied candidates to cnt.
-// STRAIGHT: the impulses without branches (contact_add, the same sums).
+// FORM: how the impulses run (the same sums).
 // PEN_FIRST (of STRAIGHT kernels): the penetrating candidates first, in
 // candidate order (the same sums), so that the second evaluation runs only
 // where a lane has two penetrating candidates, not wherever one has its second
 // (x 20 steps, without -> with: planar runner 2610 environments 149 -> 144 us,
 // biped 11700 519 -> 506, grasp 14040 1190 -> 1169, quadruped 2030 182 -> 178 but
 // 16380 370 -> 379).
-template <int REGC, bool STRAIGHT, bool PEN_FIRST>
+template <int REGC, ContactForm FORM, bool PEN_FIRST>
 __device__ __forceinline__ void ground_contacts(const ContactT* __restrict__ C, const ContactT (&Creg)[REGC], int n_con,
                                                 int max_con, const TypeT& ty, const BodyT& B, const Body& s,
                                                 const Frame& f, v3& dv, v3& dw, int& cnt) {
-  if (!STRAIGHT) {
-#pragma unroll
-    for (int k = 0; k < REGC; ++k)
-      if (k < max_con && n_con > k) cnt += contact_eval(Creg[k], ty, B, s, f, dv, dw) ? 1 : 0;
-  } else if (PEN_FIRST) {
+  if (PEN_FIRST) {
     const v3 rl0 = mul(f.R, ld3(Creg[0].l)), rl1 = mul(f.R, ld3(Creg[REGC - 1].l));
     const float d0 = Creg[0].rho - (s.p.z + rl0.z), d1 = Creg[REGC - 1].rho - (s.p.z + rl1.z);
     const bool p0 = 0 < max_con && n_con > 0 && d0 > 0.f;
     const bool p1 = 1 < max_con && n_con > 1 && d1 > 0.f;
     if (__ballot(p0 || p1))
-      contact_add(p0 ? Creg[0].rho : Creg[REGC - 1].rho, ty, B, s, f.Iwinv, sel(p0, rl0, rl1), p0 ? d0 : d1, p0 || p1, dv,
+      contact_add<FORM>(p0 ? Creg[0].rho : Creg[REGC - 1].rho, ty, B, s, f.Iwinv, sel(p0, rl0, rl1), p0 ? d0 : d1, p0 || p1, dv,
                   dw, cnt);
-    if (__ballot(p0 && p1)) contact_add(Creg[REGC - 1].rho, ty, B, s, f.Iwinv, rl1, d1, p0 && p1, dv, dw, cnt);
+    if (__ballot(p0 && p1)) contact_add<FORM>(Creg[REGC - 1].rho, ty, B, s, f.Iwinv, rl1, d1, p0 && p1, dv, dw, cnt);
   } else {
 #pragma unroll
     for (int k = 0; k < REGC; ++k) {
@@ -56,7 +57,8 @@ __device__ __forceinline__ void ground_contacts(const ContactT* __restrict__ C, 
         const v3 rl = mul(f.R, ld3(Creg[k].l));
         const float depth = Creg[k].rho - (s.p.z + rl.z);
         const bool in = n_con > k && depth > 0.f;
-        if (__ballot(in)) contact_add(Creg[k].rho, ty, B, s, f.Iwinv, rl, depth, in, dv, dw, cnt);
+        if (FORM == STRAIGHT ? __ballot(in) != 0 : in)
+          contact_add<FORM>(Creg[k].rho, ty, B, s, f.Iwinv, rl, depth, in, dv, dw, cnt);
       }
     }
   }
@@ -139,7 +141,7 @@ constexpr int tape_role(int maxdof) { return maxdof > 1 ? 1 : 0; }
 // use different ones. csrc: the children's mail rows (64: the zero row).
 // groups: the batch has contact lanes in this type. torque: the body's total
 // torque; cnt (ROLE 1): its applied contacts.
-template <int ROLE, int MAXDOF, bool PAIRS, bool CL, int REGC, bool STRAIGHT, int PAR>
+template <int ROLE, int MAXDOF, bool PAIRS, bool CL, int REGC, ContactForm FORM, int PAR>
 __device__ __forceinline__ void split_substep(const Tables* __restrict__ tab, int t, const TypeT& ty, const BodyT& B,
                                               const JointT& J, bool has_joint, const ContactT (&Creg)[REGC], int cfirst,
                                               int n_con, int max_con, int lane, int b, int base, bool groups,
@@ -178,7 +180,7 @@ __device__ __forceinline__ void split_substep(const Tables* __restrict__ tab, in
       near0 = pair_near0(XC, *pl, ps0);
     }
     const Frame f = derive_inv(B, R);
-    ground_contacts<REGC, STRAIGHT, STRAIGHT && REGC == 2 && (!CL || PAIRS)>(&tab->contact[t][cfirst], Creg, n_con, max_con, ty, B, s, f, dv, dw, cnt);
+    ground_contacts<REGC, FORM, FORM == STRAIGHT && (!CL || PAIRS)>(&tab->contact[t][cfirst], Creg, n_con, max_con, ty, B, s, f, dv, dw, cnt);
     gyro = gyro_torque(B, s, f);
     if (groups) lane_group_sums(XC, lane, base, b, ty, B, dv, dw, cnt);
     if (PAIRS && ty.np > 0) pair_phase(tab, t, *pl, XC, lane, b, base, s, f, dv, dw, cnt, near0);

@@ -338,7 +338,7 @@ __device__ __forceinline__ void split_fwd_run(const Tables* __restrict__ tab, co
     if (RECORD) wtape_state<false>(tp, s, lane);
     v3 torque;
     int cnt;
-    split_substep<ROLE, MAXDOF, PAIRS, false, REGC, straight_contacts(false, PAIRS, false, REGC), decltype(parity)::value>(tab, t, ty, B, J, has_joint, Creg, B.c0, n_con,
+    split_substep<ROLE, MAXDOF, PAIRS, false, REGC, contact_form(true, false, PAIRS, false, REGC), decltype(parity)::value>(tab, t, ty, B, J, has_joint, Creg, B.c0, n_con,
                                                                              ty.max_contacts, lane, b, base, false,
                                                                              src_parent, csrc, a, s, L, XC, pl, ps0,
                                                                              torque, cnt);
