@@ -792,9 +792,9 @@ __device__ __forceinline__ void split_run(const Tables* __restrict__ tab, const 
 // One work item per block of two wavefronts (w is block-uniform: a block past
 // the list ends as a whole, before any barrier). One-axis instances hold
 // 117 to 120 VGPRs, three-axis 161 to 168, with body-body contacts 188 to 193.
-// Environment steps and taped launches always take the three-axis code: 168,
-// the environment step with 12 to 20 B of scratch and 40 to 100 SGPRs spilled to
-// VGPR lanes in each.
+// Environment steps and taped launches always take the three-axis code: 167 to
+// 168 without body-body contacts, the environment step with 16 to 20 B of
+// scratch, and 36 to 117 SGPRs spilled to VGPR lanes.
 template <bool ONE_AXIS, bool TAPE, bool PAIRS, bool ENV, bool CL, int REGC = REG_CONTACTS,
           ContactForm FORM = contact_form(true, ONE_AXIS, PAIRS, CL, REGC)>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(PAIRS ? 2 : 3))) void k_split(const Tables* __restrict__ tab, const WaveWork* __restrict__ work,
