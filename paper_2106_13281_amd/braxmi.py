@@ -197,7 +197,7 @@ class System:
         self.n_params = list(lay.n_params[:nt])
         self.p_max = lay.p_max
         self.n_pairs = list(lay.n_pairs[:nt])                      # body-body contact candidates
-        self.vjp_lds_bytes = lay.vjp_lds_bytes                     # on-chip tape of the fused adjoint
+        self.vjp_lds_bytes = lay.vjp_lds_bytes                     # least on-chip memory of the fused adjoint
         self.vjp_params_lds_bytes = lay.vjp_params_lds_bytes
         self.lds_limit = lay.lds_limit
         self.lanes_per_env = list(lay.lanes_per_env[:nt])          # fused forward: bodies + contact lanes

@@ -21,8 +21,8 @@ struct VjpSched {
   float* const* cslot;
 };
 
-// On-chip memory (LDS) per wavefront of the recomputing fused adjoint: its
-// forward tape of every substep (TAPE_N floats per lane, 3 more with the
+// On-chip memory (LDS) per work item of the recomputing fused adjoint on one
+// wavefront, the least that a fused launch takes: its forward tape of every substep (TAPE_N floats per lane, 3 more with the
 // parameter cotangents) plus the body-body candidate lists of batches that
 // have them.
 size_t vjp_lds_bytes(const Tables& tab, int n_types, bool params);
