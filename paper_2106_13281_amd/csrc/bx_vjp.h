@@ -22,9 +22,9 @@ struct VjpSched {
 };
 
 // On-chip memory (LDS) per work item of the recomputing fused adjoint on one
-// wavefront, the least that a fused launch takes: its forward tape of every substep (TAPE_N floats per lane, 3 more with the
-// parameter cotangents) plus the body-body candidate lists of batches that
-// have them.
+// wavefront, the least that a fused launch takes: its forward tape of every
+// substep (TAPE_N floats per lane, 3 more with the parameter cotangents) plus
+// the body-body candidate lists of batches that have them.
 size_t vjp_lds_bytes(const Tables& tab, int n_types, bool params);
 // The largest LDS allocation of one workgroup on gfx950 (160 KiB), the limit
 // a host-only handle reports.
